@@ -44,6 +44,7 @@ const int kSplitMaxTile = 128 * 128;           // larger tiles' split twins spil
 
 struct Kernel {
   const KernelDesc* d;
+  int code;       // index of the first catalogue entry that runs the same code
   int occupancy;  // workgroups per CU
   int vgprs;
 };
@@ -376,6 +377,7 @@ const double kUnifyTie = 0.05;
 double roofline_s(const gdy_gemm& g);
 int split_for(const gdy_ctx* ctx, int vid, const gdy_gemm& g);
 bool active(const gdy_gemm& g);
+int code_of(const gdy_ctx* ctx, int vid);
 
 double group_cost(const gdy_ctx* ctx, int vid, const gdy_gemm* g, const std::vector<int>& grp) {
   const Kernel& k = ctx->kernels[ctx->variants[vid].kernel];
@@ -398,12 +400,15 @@ double group_cost(const gdy_ctx* ctx, int vid, const gdy_gemm* g, const std::vec
 void unify_short_group(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<int>& grp,
                        const std::vector<int>& entry, gdy_plan_t* p) {
   std::vector<int> kern;  // the GEMMs' kernels as uncapped variants, in order of first use
+  std::vector<int> codes;  // names of one kernel count once
   double t = 0.0;
   for (int i : grp) {
     if (g[i].op == GDY_OP_ADD) continue;
     t += roofline_s(g[i]);
     const int v = ctx->variants[p->variant_of[i]].uncapped;
-    if (std::find(kern.begin(), kern.end(), v) == kern.end()) kern.push_back(v);
+    if (std::find(codes.begin(), codes.end(), code_of(ctx, v)) != codes.end()) continue;
+    codes.push_back(code_of(ctx, v));
+    kern.push_back(v);
   }
   if (kern.size() < 2 || t >= kUnifyUs * 1e-6 * (double)(kern.size() - 1)) return;
   std::vector<int> cand = kern;
@@ -434,7 +439,7 @@ void unify_short_group(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<
     if (vc.second > best_f * (1.0 + kUnifyTie)) continue;
     double bound = 0.0;
     for (int i : grp)
-      if (g[i].op != GDY_OP_ADD && ctx->variants[p->variant_of[i]].uncapped == vc.first)
+      if (g[i].op != GDY_OP_ADD && code_of(ctx, p->variant_of[i]) == code_of(ctx, vc.first))
         bound += 2.0 * (double)g[i].m * (double)g[i].n * (double)g[i].k * (double)std::max(g[i].batch, 1);
     if (best < 0 || bound > best_bound || (bound == best_bound && vc.second < best_cost)) {
       best = vc.first;
@@ -653,6 +658,10 @@ bool is_add_variant(const gdy_ctx* ctx, int vid) {
   return ctx->kernels[ctx->variants[vid].kernel].d->ew != 0;
 }
 
+// The kernel a variant runs, as the index of the first catalogue entry of that
+// code (several names may run one kernel).
+int code_of(const gdy_ctx* ctx, int vid) { return ctx->kernels[ctx->variants[vid].kernel].code; }
+
 // Dispatches of one group (members in launch order, GEMMs before adds,
 // variants bound): GEMMs of the same kernel share a dispatch, at most
 // kMaxFused each, numbered in order of first use.  An element-wise add
@@ -664,7 +673,7 @@ bool is_add_variant(const gdy_ctx* ctx, int vid) {
 void form_dispatches(const gdy_ctx* ctx, const std::vector<int>& members, int S, gdy_plan_t* p) {
   std::vector<int> kern, id, cnt;
   for (int i : members) {
-    const int k = ctx->variants[p->variant_of[i]].kernel;
+    const int k = code_of(ctx, p->variant_of[i]);
     int d = -1;
     if (is_add_variant(ctx, p->variant_of[i]) && !kern.empty() && !ctx->kernels[kern[0]].d->ew &&
         cnt[0] < kMaxFused)
@@ -1053,7 +1062,7 @@ void make_plan_core(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int 
     uncap_mixed_group(ctx, g, grp, p);
     unify_short_group(ctx, g, grp, entry, p);
     for (int i : grp) {
-      const int k = ctx->variants[p->variant_of[i]].kernel;
+      const int k = code_of(ctx, p->variant_of[i]);
       size_t u = 0;
       while (u < kern.size() && kern[u] != k) ++u;
       if (u == kern.size()) {
@@ -1690,6 +1699,9 @@ static gdy_status create_impl(gdy_ctx* ctx, int device, const char* table_path, 
         k.vgprs = attr.numRegs;
       }
       const int kid = (int)ctx->kernels.size();
+      k.code = kid;
+      for (int e = kid; e-- > 0;)
+        if (ctx->kernels[e].d->func == k.d->func) k.code = e;
       ctx->kernels.push_back(k);
       for (int c = 0; c < kNumCaps; ++c) {
         if (k.d->ew && kCaps[c] != 0) continue;  // the element-wise add has no grid caps

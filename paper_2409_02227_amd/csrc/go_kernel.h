@@ -339,19 +339,21 @@ template <bool KCONT, int ES, int ROWS, int NT> struct StageSel;
 template <int ES, int ROWS, int NT> struct StageSel<true, ES, ROWS, NT> { typedef StageK<ES, ROWS, NT> T; };
 template <int ES, int ROWS, int NT> struct StageSel<false, ES, ROWS, NT> { typedef StageT<ES, ROWS, NT> T; };
 
-// fp32 -> output element, round to nearest even.
-template <int DT> __device__ __forceinline__ uint16_t to_out(float x);
-template <> __device__ __forceinline__ uint16_t to_out<DT_F16>(float x) {
-  return __builtin_bit_cast(uint16_t, (_Float16)x);
+// fp32 -> output elements, round to nearest even, by the conversion
+// instructions (two elements each; rounding by integer arithmetic took six
+// operations an element, 3 us of a 256 x 256 tile's epilogue).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+template <int DT> __device__ __forceinline__ unsigned to_out2(float lo, float hi) {
+  const f32x2 x = {lo, hi};
+  if constexpr (DT == DT_F16) return __builtin_bit_cast(unsigned, __builtin_convertvector(x, f16x2));
+  else return __builtin_bit_cast(unsigned, __builtin_convertvector(x, bf16x2));
 }
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float x) {
-  unsigned u = __builtin_bit_cast(unsigned, x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // quiet NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+template <int DT> __device__ __forceinline__ uint16_t to_out(float x) {
+  if constexpr (DT == DT_F16) return __builtin_bit_cast(uint16_t, (_Float16)x);
+  else return __builtin_bit_cast(uint16_t, (__bf16)x);
 }
-template <> __device__ __forceinline__ uint16_t to_out<DT_BF16>(float x) { return f32_to_bf16_rne(x); }
-template <> __device__ __forceinline__ uint16_t to_out<DT_FP8>(float x) { return f32_to_bf16_rne(x); }
 
 // One output element at byte offset `off` of C (fp32 results are stored as is).
 template <int DT> __device__ __forceinline__ void store_out(float x, Rsrc rc, int off) {
@@ -570,8 +572,8 @@ __global__ void __launch_bounds__(256) split_reduce(KLaunch L) {
     if constexpr (OUT != DT_F32) {  // four 16-bit outputs in one 8-byte store
       if (cols == 4 && p.c_vec) {
         u32x2 w;
-        w[0] = (unsigned)to_out<OUT>(acc[0] * p.scale) | ((unsigned)to_out<OUT>(acc[1] * p.scale) << 16);
-        w[1] = (unsigned)to_out<OUT>(acc[2] * p.scale) | ((unsigned)to_out<OUT>(acc[3] * p.scale) << 16);
+        w[0] = to_out2<OUT>(acc[0] * p.scale, acc[1] * p.scale);
+        w[1] = to_out2<OUT>(acc[2] * p.scale, acc[3] * p.scale);
         __builtin_amdgcn_raw_buffer_store_b64(w, rc, off, 0, 0);
         stored = true;
       }

@@ -68,10 +68,12 @@ __device__ __forceinline__ sdesc make_sdesc(const void* base, int bytes) {
 }
 
 // One 16-byte copy per lane: global byte `voffset` of `d` -> LDS address
-// lds_addr + 16 * lane (lds_addr is wave-uniform).
+// lds_addr + 16 * lane (lds_addr is wave-uniform).  The s_nop is the wait
+// state a copy to LDS needs after the write of M0 (the compiler inserts none
+// in front of inline assembly).
 __device__ __forceinline__ void copy16_to_lds(sdesc d, const lds_u8* lds_base, int voffset) {
   const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds_base);
-  asm volatile("buffer_load_dwordx4 %1, %2, 0 offen lds"
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :
                : "{m0}"(lds_addr), "v"(voffset), "s"(d)
                : "memory");
@@ -581,22 +583,18 @@ go_gemm_d(KLaunch L) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int col = n0 + wn * C::WTN + j * 32 + 8 * g + 4 * (lane >> 5);
-          const uint16_t h0 = to_out<DT>(acc[j][i][4 * g + 0] * s);
-          const uint16_t h1 = to_out<DT>(acc[j][i][4 * g + 1] * s);
-          const uint16_t h2 = to_out<DT>(acc[j][i][4 * g + 2] * s);
-          const uint16_t h3 = to_out<DT>(acc[j][i][4 * g + 3] * s);
+          u32x2 v;
+          v[0] = to_out2<DT>(acc[j][i][4 * g + 0] * s, acc[j][i][4 * g + 1] * s);
+          v[1] = to_out2<DT>(acc[j][i][4 * g + 2] * s, acc[j][i][4 * g + 3] * s);
           if (row < Mrows) {
             const int off = row * ldc_b + col * 2;
             if (col + 4 <= Ncols && p.c_vec) {
-              u32x2 v;
-              v[0] = (unsigned)h0 | ((unsigned)h1 << 16);
-              v[1] = (unsigned)h2 | ((unsigned)h3 << 16);
               __builtin_amdgcn_raw_buffer_store_b64(v, rc, off, 0, 0);
             } else {
-              if (col + 0 < Ncols) __builtin_amdgcn_raw_buffer_store_b16(h0, rc, off + 0, 0, 0);
-              if (col + 1 < Ncols) __builtin_amdgcn_raw_buffer_store_b16(h1, rc, off + 2, 0, 0);
-              if (col + 2 < Ncols) __builtin_amdgcn_raw_buffer_store_b16(h2, rc, off + 4, 0, 0);
-              if (col + 3 < Ncols) __builtin_amdgcn_raw_buffer_store_b16(h3, rc, off + 6, 0, 0);
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (col + e < Ncols)
+                  __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[e / 2] >> (16 * (e & 1))), rc, off + 2 * e, 0, 0);
             }
           }
         }

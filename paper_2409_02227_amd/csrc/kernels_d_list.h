@@ -3,10 +3,10 @@
 // in kernels_list.h holds the same tiles for GEMMs the direct kernels cannot
 // take (K not a multiple of the K tile, unaligned).
 #define GDY_TILES_D(L, TA, TB)                                        \
-  GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 256, 256, 2, 4, 2),     \
-  GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 256, 256, 2, 2, 2),     \
-  GDY_KERNEL_DH(GDY_DT, GDY_DTNAME, TA, TB, L, 256, 256, 2, 4, 4),    \
-  GDY_KERNEL_DH(GDY_DT, GDY_DTNAME, TA, TB, L, 256, 256, 2, 2, 4),    \
+  GDY_KERNEL_P(GDY_DT, GDY_DTNAME, TA, TB, L, "w2x4_d2", 128),        \
+  GDY_KERNEL_P(GDY_DT, GDY_DTNAME, TA, TB, L, "w2x2_d2", 128),        \
+  GDY_KERNEL_P(GDY_DT, GDY_DTNAME, TA, TB, L, "w2x4_d4h", 64),        \
+  GDY_KERNEL_P(GDY_DT, GDY_DTNAME, TA, TB, L, "w2x2_d4h", 64),        \
   GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 256, 128, 2, 2, 3),     \
   GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 128, 256, 2, 2, 3),     \
   GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 128, 128, 2, 2, 2),     \
@@ -34,19 +34,18 @@
   GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 64, 128, 2, 2, 4),      \
   GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 64, 64, 2, 2, 4)
 
-// 16 waves of 64x64 (4 per SIMD): 16-bit types only (fp8 fragments are
-// twice as wide and would not fit in 128 registers).
+// A further 256 x 256 name of the 16-bit types.
 #if GDY_DT16
-#define GDY_TILES_D_WIDE(L, TA, TB) GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 256, 256, 4, 4, 2),
+#define GDY_TILES_D_WIDE(L, TA, TB) GDY_KERNEL_P(GDY_DT, GDY_DTNAME, TA, TB, L, "w4x4_d2", 128),
 #else
 #define GDY_TILES_D_WIDE(L, TA, TB)
 #endif
 
 static const ::gdy::KernelDesc kTableD[] = {
-    GDY_TILES_D_WIDE("nn", 0, 0)
-    GDY_TILES_D_WIDE("nt", 0, 1)
     GDY_TILES_D("nn", 0, 0),
     GDY_TILES_D("nt", 0, 1),
+    GDY_TILES_D_WIDE("nn", 0, 0)
+    GDY_TILES_D_WIDE("nt", 0, 1)
     GDY_TILES_D_SMALL("tn", 1, 0),
     GDY_TILES_D_SMALL("tt", 1, 1),
     GDY_TILES_D_LAT("nn", 0, 0),
