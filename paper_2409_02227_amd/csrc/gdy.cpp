@@ -1110,6 +1110,15 @@ bool vec_ok(const void* ptr, int64_t ld, int es, bool kcontiguous, int64_t item_
   return a % v == 0 && (ld * es) % v == 0 && item_stride_bytes % v == 0;
 }
 
+// Direct copies to LDS move 16-byte chunks: the base, the row pitch and the
+// item stride must be multiples of 16 bytes.  A K-contiguous operand's K must
+// be whole chunks (chunks past K read as zeros); k-major rows past K lie past
+// the extent and read as zeros whatever K is.
+bool copies_ok(const void* ptr, int64_t ld, int64_t k, int es, bool kcontiguous, int64_t item_stride) {
+  return (uintptr_t)ptr % 16 == 0 && (ld * es) % 16 == 0 && (item_stride * es) % 16 == 0 &&
+         (!kcontiguous || (k * es) % 16 == 0);
+}
+
 // Buffer size for reads: the extent rounded up to the end of the dword that
 // holds its last byte.  The buffer unit drops a multi-dword read's dwords
 // that end past the size, so an exact size would zero a last element that
@@ -1156,6 +1165,8 @@ KArgs make_args(const gdy_ctx* ctx, int vid, const gdy_gemm& g, Geometry* geo_ou
   a.b_vec = (g.k > 0 || add) && vec_ok(g.b, g.ldb, es, add || g.trans_b == 1, batched ? g.stride_b * es : 0);
   a.c_vec = (uintptr_t)g.c % 8 == 0 && (g.ldc * out_size(g)) % 8 == 0 &&
             (!batched || (g.stride_c * out_size(g)) % 8 == 0);
+  a.a_dma = copies_ok(g.a, g.lda, g.k, es, g.trans_a == 0, batched ? g.stride_a : 0);
+  a.b_dma = copies_ok(g.b, g.ldb, g.k, es, g.trans_b == 1, batched ? g.stride_b : 0);
   a.group_m = 8;
   a.xcd_remap = 1;
   a.batch = (int32_t)std::max(g.batch, 1);

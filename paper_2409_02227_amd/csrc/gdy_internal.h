@@ -28,6 +28,8 @@ struct KArgs {
   int32_t a_vec;      // 1: A base and rows are aligned for vector loads
   int32_t b_vec;      // 1: same for B
   int32_t c_vec;      // 1: C base and rows allow 8-byte stores
+  int32_t a_dma;      // 1: A takes direct 16-byte copies to LDS (base, pitch and item stride
+  int32_t b_dma;      //    aligned; K-contiguous: K whole chunks); b_dma: same for B
   int32_t group_m;    // tile-order swizzle: tile rows per group
   int32_t xcd_remap;  // 1: keep consecutive tiles on one XCD
   int32_t batch;      // items of a strided batch (>= 1); the extents above are per item

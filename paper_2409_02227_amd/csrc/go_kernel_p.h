@@ -149,6 +149,44 @@ template <int ES, bool KC> struct PhaseCopy {
   }
 };
 
+// The rounded BM x BN tile in LDS at `out` (rows of PITCH bytes) to C, all
+// threads of the workgroup: 16 bytes a lane, or single elements where C's rows
+// have no 8-byte alignment.  rows, cols: what of the tile lies inside C; off:
+// its first byte.
+template <int BN, int NT, int PITCH>
+__device__ __forceinline__ void store_tile(const lds_u8* out, Rsrc rc, int off, int ldc_b, int rows, int cols,
+                                           bool vec, int tid) {
+  constexpr int LPR = BN / 8;  // lanes per row
+  if (vec) {
+    const int c8 = (tid % LPR) * 8;
+    const int left = cols - c8;  // columns from this lane's first one
+#pragma unroll 4
+    for (int r = tid / LPR; r < rows; r += NT / LPR) {
+      const u32x4 v = lds_read16(out + r * PITCH + c8 * 2);
+      const int o = off + r * ldc_b + c8 * 2;
+      if (left >= 8) {
+        __builtin_amdgcn_raw_buffer_store_b128(v, rc, o, 0, 0);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (e < left)
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[e / 2] >> (16 * (e & 1))), rc, o + 2 * e, 0, 0);
+      }
+    }
+  } else {
+    const int lane = tid & 63;
+    for (int r = tid / 64; r < rows; r += NT / 64)
+#pragma unroll
+      for (int e = 0; e < BN / 64; ++e) {
+        const int c = e * 64 + lane;
+        if (c < cols)
+          __builtin_amdgcn_raw_buffer_store_b16(
+              *(const __attribute__((address_space(3))) uint16_t*)(out + r * PITCH + c * 2), rc,
+              off + r * ldc_b + c * 2, 0, 0);
+      }
+  }
+}
+
 template <int DT, int TA, int TB>
 __global__ void __launch_bounds__(512)
 go_gemm_p(KLaunch L) {
@@ -348,34 +386,8 @@ go_gemm_p(KLaunch L) {
           }
     }
     __syncthreads();
-    const int rows = min(half ? 128 : 256, Mrows - m0);
-    if (p.c_vec) {
-      const int c8 = (lane & 31) * 8;
-      const int left = Ncols - (n0 + c8);  // columns from this lane's first one
-#pragma unroll 4
-      for (int r = wave * 2 + (lane >> 5); r < rows; r += 16) {
-        const u32x4 v = lds_read16(smem + r * kPOutRow + c8 * 2);
-        const int off = (m0 + r) * ldc_b + (n0 + c8) * 2;
-        if (left >= 8) {
-          __builtin_amdgcn_raw_buffer_store_b128(v, rc, off, 0, 0);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (e < left)
-              __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[e / 2] >> (16 * (e & 1))), rc, off + 2 * e, 0, 0);
-        }
-      }
-    } else {  // rows of any alignment: 64 consecutive elements an instruction
-      for (int r = wave; r < rows; r += 8)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int c = e * 64 + lane;
-          if (n0 + c < Ncols)
-            __builtin_amdgcn_raw_buffer_store_b16(
-                *(const __attribute__((address_space(3))) uint16_t*)(smem + r * kPOutRow + c * 2), rc,
-                (m0 + r) * ldc_b + (n0 + c) * 2, 0, 0);
-        }
-    }
+    store_tile<256, 512, kPOutRow>(smem, rc, m0 * ldc_b + n0 * 2, ldc_b, min(half ? 128 : 256, Mrows - m0),
+                                   min(256, Ncols - n0), p.c_vec != 0, (int)threadIdx.x);
     if (tb + nwg < total) __syncthreads();  // the next tile's copies overwrite the output rows
   }
 }

@@ -1,0 +1,362 @@
+// go_kernel_u.h -- GO-Kernels for operands of any size and alignment (16-bit
+// and 8-bit types): the kernels the planner binds where K is no whole number of
+// K tiles, or a base, row pitch or item stride no multiple of 16 bytes.
+//
+// Both operands lie in LDS as the buffer unit's direct copies leave them (the
+// swizzled layouts below), and each operand gets there by one of two ways,
+// chosen per GEMM:
+//  * copies: base, pitch and item stride multiples of 16 bytes (and, for a
+//    K-contiguous operand, K whole 16-byte chunks): direct global -> LDS
+//    copies; chunks past K are sent out of range and read as zeros;
+//  * registers: anything else.  A lane loads the five dwords around its 16
+//    bytes (dword-aligned: what a buffer load needs), shifts them into place
+//    with v_alignbit, zeroes what lies past K and writes the chunk to the same
+//    place of the same layout.  K-major operands stay k-major: the transpose
+//    is left to the LDS reads.
+// What bounds it: the kernels it replaced loaded unaligned operands element by
+// element (8 or 16 loads a chunk instead of 2) and transposed k-major operands
+// in registers.
+//
+// Two K tiles in LDS, one barrier per K tile: tile kt+1 goes to LDS while kt
+// is computed, and in the register way tile kt+2 is being loaded, so a load has
+// a whole tile's time to arrive.  16 x 16 MFMAs; the rounded tile leaves
+// through LDS as whole rows.
+#pragma once
+#include "go_kernel_p.h"
+
+namespace gdy {
+
+// k-major tile of ROWS elements per k-row: 16-byte chunk c of row k at position
+// c ^ h(k).  A transpose read takes, 32 lanes at a time, 16 columns of 4
+// (16-bit: two chunks) or 8 (8-bit: one chunk) consecutive k-rows for two
+// groups of lanes whose k differ by 8 (32).  Rows of 256 bytes and more all
+// start on bank 0, shorter ones on the bank their k gives; h spreads those that
+// share banks over different chunks (rows of 16 or 32 bytes, the transposed A
+// of 16-row tiles, keep their order: two lanes to a bank).
+template <int ES, int ROWS> struct TileT {
+  static constexpr int RB = ROWS * ES;
+  static constexpr int NCH = RB / 16;
+  static_assert(RB >= 16 && RB <= 512, "1 to 32 chunks per k-row");
+  static __device__ __forceinline__ int h(int k) {
+    if constexpr (RB < 64) {
+      return 0;
+    } else if constexpr (ES == 2) {
+      if constexpr (RB >= 256) return (4 * (k & 3)) ^ (2 * ((k >> 3) & 1));
+      else if constexpr (RB == 128) return (2 * ((k >> 1) & 1)) ^ (4 * ((k >> 3) & 1));
+      else return 2 * ((k >> 3) & 1);
+    } else {
+      if constexpr (RB >= 256) return (2 * (k & 7)) ^ ((k >> 5) & 1);
+      else if constexpr (RB == 128) return (2 * ((k >> 1) & 3)) ^ ((k >> 5) & 1);
+      else return (2 * ((k >> 2) & 1)) ^ ((k >> 5) & 1);
+    }
+  }
+  static __device__ __forceinline__ int addr(int k, int col) {
+    const int byte = col * ES;
+    return k * RB + (((byte >> 4) ^ h(k)) << 4) + (byte & 15);
+  }
+  // per-lane offset of sub-read hh of a 16-column fragment at K step 0
+  static __device__ __forceinline__ int lane_off(int lane, int col0, int hh) {
+    const int L = lane & 15, kb = (lane >> 4) * (FragT<ES>::FB / ES);
+    if constexpr (ES == 2) return addr(kb + 4 * hh + (L >> 2), col0 + 4 * (L & 3));
+    else return addr(kb + 8 * hh + (L >> 1), col0 + 8 * (L & 1));
+  }
+};
+
+// One operand of a tile: ROWS rows (or columns) x 128 bytes of K, KC:
+// K-contiguous.  Lane `lane` of wave `wave` owns the chunks at LDS bytes
+// (wave + NW*j)*1024 + lane*16 in both ways.
+template <int ES, bool KC, int ROWS, int NW> struct Operand {
+  static constexpr int BLOCKS = ROWS / 8;                   // 1 KiB copies of a K tile
+  static constexpr int N = BLOCKS < NW ? 1 : BLOCKS / NW;   // chunks per lane
+  static constexpr bool ALL = BLOCKS >= NW;                 // every wave takes part (16-row tiles: two do)
+  static constexpr int BK = 128 / ES;
+  static_assert(ROWS % 8 == 0 && (BLOCKS < NW || BLOCKS % NW == 0), "whole copies per wave");
+  typedef TileT<ES, ROWS> T;
+  const uint8_t* base;  // of the item and K run, down to a dword
+  int bytes;            // from base to the end of the dword that holds the operand's last byte
+  int step;             // bytes from one K tile to the next
+  int jstep;            // bytes between this lane's chunks (K-contiguous)
+  int off[KC ? 1 : N];  // byte offset of the lane's chunk(s) in K tile 0
+  int kpos[KC ? 1 : N]; // K-contiguous: K byte of the chunk; k-major: its k
+  u32x4 lo[N];
+  unsigned hi[N];
+
+  // extent: the operand's bytes from p on (items of a batch and K runs start at
+  // any alignment, so the rounding up to whole dwords is this item's own)
+  __device__ __forceinline__ void init(const uint8_t* p, int extent, int ld_b, int row0, int wave, int lane) {
+    const int mis = (int)((uintptr_t)p & 3);
+    base = p - mis;
+    bytes = (extent + mis + 3) & ~3;
+    step = KC ? 128 : BK * ld_b;
+    jstep = 8 * NW * ld_b;
+    if constexpr (KC) {
+      const int r = wave * 8 + lane / 8;  // the swizzle of row r + 8*NW*j is that of row r (8*NW/2 = 0 mod 8)
+      const int c = (lane & 7) ^ ((r >> 1) & 7);
+      off[0] = (row0 + r) * ld_b + c * 16 + mis;
+      kpos[0] = c * 16;
+    } else {
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const int q = (wave + NW * j) * 64 + lane;
+        const int k = q / T::NCH;
+        off[j] = k * ld_b + row0 * ES + ((q % T::NCH) ^ T::h(k)) * 16 + mis;
+        kpos[j] = k;
+      }
+    }
+  }
+  __device__ __forceinline__ int at(int j) const { return KC ? off[0] + j * jstep : off[KC ? 0 : j]; }
+
+  __device__ __forceinline__ void copy(int kt, int kbytes, lds_u8* dst, int wave) const {
+    if (!ALL && wave >= BLOCKS) return;
+    const sdesc d = make_sdesc(base + (int64_t)kt * step, bytes - kt * step);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      int o = at(j);
+      if constexpr (KC) o = kpos[0] < kbytes - kt * 128 ? o : kOutOfRange;
+      copy16_to_lds(d, dst + (wave + NW * j) * 1024, o);
+    }
+  }
+  __device__ __forceinline__ void load(int kt, int wave) {
+    if (!ALL && wave >= BLOCKS) return;
+    const Rsrc r = make_rsrc(base + (int64_t)kt * step, bytes - kt * step);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int o = at(j) & ~3;
+      lo[j] = __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0);
+      hi[j] = __builtin_amdgcn_raw_buffer_load_b32(r, o + 16, 0, 0);
+    }
+  }
+  // K: elements of the run
+  __device__ __forceinline__ void store(int kt, int K, lds_u8* dst, int wave, int lane) const {
+    if (!ALL && wave >= BLOCKS) return;
+    const int left = K - kt * BK;  // elements of K from this tile on
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const unsigned sh = (unsigned)(at(j) & 3) * 8;
+      u32x4 v;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v[w] = __builtin_amdgcn_alignbit(w < 3 ? lo[j][w + 1] : hi[j], lo[j][w], sh);
+      if (left < BK) {  // the last, partial tile
+        if constexpr (KC) {
+          const int nv = left * ES - kpos[0];  // bytes of this chunk below K
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const int b = nv - 4 * w;
+            v[w] &= b >= 4 ? 0xffffffffu : b <= 0 ? 0u : (1u << (8 * b)) - 1u;
+          }
+        } else if (kpos[KC ? 0 : j] >= left) {
+          v = u32x4{0u, 0u, 0u, 0u};
+        }
+      }
+      *(__attribute__((address_space(3))) u32x4*)(dst + (wave + NW * j) * 1024 + lane * 16) = v;
+    }
+  }
+};
+
+template <int DT, int BM, int BN, int WM, int WN> struct UCfg {
+  static constexpr int ES = ElemSize<DT>::v;
+  static constexpr int BK = 128 / ES;
+  static constexpr int NW = WM * WN;
+  static constexpr int FM = BM / WM / 16, FN = BN / WN / 16;
+  static constexpr int NKS = 128 / (4 * FragT<ES>::FB);  // MFMA K steps per tile
+  static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128;
+  static constexpr int STAGE = A_BYTES + B_BYTES;
+  static constexpr int PITCH = BN * 2 + 16;  // of the rounded tile: a half wave's 16 rows on distinct banks
+  static constexpr int LDS = 2 * STAGE > BM * PITCH ? 2 * STAGE : BM * PITCH;
+  static_assert(BM % (WM * 16) == 0 && BN % (WN * 16) == 0, "wave tile must hold whole 16 x 16 blocks");
+  static_assert(LDS <= 160 * 1024, "LDS budget");
+};
+
+template <int DT, int TA, int TB, int BM, int BN, int WM, int WN, bool SPLIT>
+__global__ void __launch_bounds__(WM * WN * 64)
+go_gemm_u(KLaunch L) {
+  typedef UCfg<DT, BM, BN, WM, WN> C;
+  typedef Mma<DT, 16> M;
+  typedef typename FragT<C::ES>::T Frag;
+  typedef typename M::Acc Acc;
+  typedef Operand<C::ES, TA == 0, BM, C::NW> OpA;
+  typedef Operand<C::ES, TB == 1, BN, C::NW> OpB;
+  constexpr int NHH = C::ES == 2 ? 2 : 4;
+  constexpr int WTM = BM / WM, WTN = BN / WN;
+
+  __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[C::LDS];
+  lds_u8* smem = (lds_u8*)smem_raw;
+
+  int gi, lwg, nwg;
+  locate(L, gi, lwg, nwg);
+  if (gi < 0) return;  // an idle slot of a placed dispatch
+  const KArgs& p = L.g[gi];
+  if (p.ew) {  // an element-wise add fused into this dispatch
+    ew_member<C::NW * 64>(p, lwg, nwg);
+    return;
+  }
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int ntiles = p.tiles_m * p.tiles_n;
+  const int lda_b = (int)p.lda * C::ES, ldb_b = (int)p.ldb * C::ES, ldc_b = (int)p.ldc * 2;
+  const int Mrows = (int)p.m, Ncols = (int)p.n;
+  const bool acopy = p.a_dma, bcopy = p.b_dma;
+  const int a_extent = TA == 0 ? (Mrows - 1) * lda_b + (int)p.k * C::ES : ((int)p.k - 1) * lda_b + Mrows * C::ES;
+  const int b_extent = TB == 1 ? (Ncols - 1) * ldb_b + (int)p.k * C::ES : ((int)p.k - 1) * ldb_b + Ncols * C::ES;
+
+  const int kc0 = pk_lane<C::ES>(lane, 0), kc1 = pk_lane<C::ES>(lane, 1);
+  int aoff[C::FM][NHH], boff[C::FN][NHH];
+  if constexpr (TA == 1) {
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+      for (int hh = 0; hh < NHH; ++hh) aoff[i][hh] = OpA::T::lane_off(lane, wm * WTM + i * 16, hh);
+  }
+  if constexpr (TB == 0) {
+#pragma unroll
+    for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+      for (int hh = 0; hh < NHH; ++hh) boff[j][hh] = OpB::T::lane_off(lane, wn * WTN + j * 16, hh);
+  }
+
+  // work items: every tile of every item of a strided batch; in the split
+  // twin, each in `split` K runs (split innermost)
+  const int nsplit = SPLIT ? p.split : 1;
+  const int total = ntiles * p.batch * nsplit;
+  for (int tb = lwg; tb < total; tb += nwg) {
+    const int s_run = SPLIT ? tb % nsplit : 0;
+    const int tile_all = SPLIT ? tb / nsplit : tb;
+    const int item = tile_all / ntiles;
+    const int t = tile_all - item * ntiles;
+    int K = (int)p.k;
+    int64_t a_shift = 0, b_shift = 0;
+    if (SPLIT && nsplit > 1) {  // this run's K range: operands start at its first K tile
+      const int k0 = split_k0(p, s_run, C::BK);
+      K = min(K - k0, p.split_kt * C::BK);
+      a_shift = TA == 0 ? (int64_t)k0 * C::ES : (int64_t)k0 * lda_b;
+      b_shift = TB == 1 ? (int64_t)k0 * C::ES : (int64_t)k0 * ldb_b;
+    }
+    const Rsrc rc = make_rsrc(p.c + item * p.stride_c, p.c_bytes);
+    const int nk = (K + C::BK - 1) / C::BK;
+    int tm, tn;
+    tile_coords(t, p, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+
+    OpA oa;
+    OpB ob;
+    oa.init(p.a + item * p.stride_a + a_shift, a_extent - (int32_t)a_shift, lda_b, m0, wave, lane);
+    ob.init(p.b + item * p.stride_b + b_shift, b_extent - (int32_t)b_shift, ldb_b, n0, wave, lane);
+
+    Acc acc[C::FN][C::FM];  // C^T blocks: [n block][m block]
+#pragma unroll
+    for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+      for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+        for (int r = 0; r < M::NACC; ++r) acc[j][i][r] = 0.f;
+
+    if (nk > 0) {
+      // tile kt to its stage (register way: the values loaded before), and the
+      // loads of the tile after it
+      auto stage_in = [&](int kt) {
+        lds_u8* st = smem + (kt & 1) * C::STAGE;
+        if (acopy) {
+          oa.copy(kt, K * C::ES, st, wave);
+        } else {
+          oa.store(kt, K, st, wave, lane);
+          if (kt + 1 < nk) oa.load(kt + 1, wave);
+        }
+        if (bcopy) {
+          ob.copy(kt, K * C::ES, st + C::A_BYTES, wave);
+        } else {
+          ob.store(kt, K, st + C::A_BYTES, wave, lane);
+          if (kt + 1 < nk) ob.load(kt + 1, wave);
+        }
+      };
+      if (!acopy) oa.load(0, wave);
+      if (!bcopy) ob.load(0, wave);
+      stage_in(0);
+      for (int kt = 0; kt < nk; ++kt) {
+        // this wave's part of tile kt is in LDS and its reads of tile kt-1 are
+        // done; past the barrier that holds for every wave
+        wait_vmcnt<0>();
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+        barrier_nowait();
+        __builtin_amdgcn_sched_barrier(0);
+        const lds_u8* As = smem + (kt & 1) * C::STAGE;
+        const lds_u8* Bs = As + C::A_BYTES;
+#pragma unroll
+        for (int ks = 0; ks < C::NKS; ++ks) {
+          Frag af[C::FM], bf[C::FN];
+#pragma unroll
+          for (int j = 0; j < C::FN; ++j) {
+            if constexpr (TB == 1) bf[j] = pk_frag<C::ES>(Bs + (wn * WTN + j * 16) * 128, kc0, kc1, ks);
+            else bf[j] = frag_t<C::ES, typename OpB::T>(Bs + (C::ES == 2 ? ks * 32 * OpB::T::RB : 0), boff[j], 0);
+          }
+#pragma unroll
+          for (int i = 0; i < C::FM; ++i) {
+            if constexpr (TA == 0) af[i] = pk_frag<C::ES>(As + (wm * WTM + i * 16) * 128, kc0, kc1, ks);
+            else af[i] = frag_t<C::ES, typename OpA::T>(As + (C::ES == 2 ? ks * 32 * OpA::T::RB : 0), aoff[i], 0);
+          }
+          if (ks == 0 && kt + 1 < nk) stage_in(kt + 1);
+#pragma unroll
+          for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+            for (int i = 0; i < C::FM; ++i) acc[j][i] = M::run(bf[j], af[i], acc[j][i]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+
+    if constexpr (SPLIT) {
+      if (nsplit > 1) {  // the run's unscaled fp32 partial into its plane
+        float* P = split_plane(p, item, s_run);
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+          for (int i = 0; i < C::FM; ++i) {
+            const int row = m0 + wm * WTM + i * 16 + (lane & 15);
+            const int col = n0 + wn * WTN + j * 16 + 4 * (lane >> 4);
+            if (row >= Mrows) continue;
+            float* dst = P + (size_t)row * Ncols + col;
+            if (col + 4 <= Ncols && (Ncols & 3) == 0) {
+              *reinterpret_cast<float4*>(dst) = make_float4(acc[j][i][0], acc[j][i][1], acc[j][i][2], acc[j][i][3]);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (col + e < Ncols) dst[e] = acc[j][i][e];
+            }
+          }
+        __syncthreads();  // every wave is done with the stages before the next item refills them
+        continue;
+      }
+    }
+
+    // accumulator r of lane l is n = 4*(l/16) + r, m = l%16 of its block
+    __syncthreads();  // every wave has read its last fragments
+    const float s = p.scale;
+#pragma unroll
+    for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+      for (int i = 0; i < C::FM; ++i) {
+        const Acc& x = acc[j][i];
+        const u32x2 v = {to_out2<DT>(x[0] * s, x[1] * s), to_out2<DT>(x[2] * s, x[3] * s)};
+        *(__attribute__((address_space(3))) u32x2*)(smem + (wm * WTM + i * 16 + (lane & 15)) * C::PITCH +
+                                                    (wn * WTN + j * 16 + 4 * (lane >> 4)) * 2) = v;
+      }
+    __syncthreads();
+    store_tile<BN, C::NW * 64, C::PITCH>(smem, rc, m0 * ldc_b + n0 * 2, ldc_b, min(BM, Mrows - m0),
+                                         min(BN, Ncols - n0), p.c_vec != 0, tid);
+    if (tb + nwg < total) __syncthreads();  // the next tile's copies overwrite the output rows
+  }
+}
+
+}  // namespace gdy
+
+// Catalogue entries, under the names of the register-staged family (same tiles;
+// the suffix named its MFMA block).
+#define GDY_KERNEL_U(DT, DTNAME, TA, TB, LAYOUT, BM, BN, WM, WN, MM)                              \
+  {DTNAME "_" LAYOUT "_" #BM "x" #BN "_w" #WM "x" #WN "_m" #MM,                                    \
+   DT, TA, TB, BM, BN, ::gdy::UCfg<DT, BM, BN, WM, WN>::BK, WM * WN,                               \
+   16, ::gdy::UCfg<DT, BM, BN, WM, WN>::LDS,                                                        \
+   reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, false>), 0, 0,       \
+   reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, true>)}

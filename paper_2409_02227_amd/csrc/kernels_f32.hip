@@ -3,6 +3,7 @@
 #include "go_kernel.h"
 #define GDY_DT ::gdy::DT_F32
 #define GDY_DTNAME "f32"
+#define GDY_DT32 1
 #include "kernels_list.h"
 int gdy::kernels_f32(const KernelDesc** out) {
   *out = kTable;
