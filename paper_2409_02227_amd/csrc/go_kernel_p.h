@@ -1,7 +1,8 @@
 // go_kernel_p.h -- the 256 x 256 GO-Kernel on two alternating wave groups.
 //
-// Same GEMM, storage reading and operand requirements as the direct family
-// (go_kernel_d.h); K only has to fill whole 16-byte chunks.  Eight waves
+// Same GEMM and storage reading as go_kernel.h, operands and LDS layouts as in
+// lds_copy.h: 16-byte aligned bases, pitches and item strides, and K whole
+// 16-byte chunks where it is contiguous.  Eight waves
 // compute a tile, two per SIMD, one of each group (waves 0-3 and 4-7).  While
 // one group issues the MFMAs of a quarter of its K tile, the other reads the
 // fragments of its next quarter from LDS and issues its copies; a barrier ends
@@ -47,7 +48,7 @@
 // (six), after that.
 // Copies past the last K tile read nothing (out of range) and keep the count.
 #pragma once
-#include "go_kernel_d.h"
+#include "lds_copy.h"
 
 namespace gdy {
 
@@ -55,51 +56,6 @@ constexpr int kPHalf = 16 * 1024;          // bytes of a half tile
 constexpr int kPLds = 9 * kPHalf;          // 2 x (A0 A1 B0 B1), or 3 x (A0 B0 B1)
 constexpr int kPOutRow = 528;              // row pitch of the rounded tile in LDS
 static_assert(256 * kPOutRow <= kPLds, "the rounded tile fits in the ring");
-constexpr int kOutOfRange = 0x7ffffff0;    // past any operand's extent: the copy writes zeros
-
-// k-major half tile: BK rows (one per k) of 128 elements, 16-byte chunk c of
-// row k at position c ^ h(k).  A transpose read is serviced 32 lanes at a
-// time: 16 columns of 4 (16-bit) or 8 (8-bit) consecutive k-rows for two
-// groups of lanes whose k differ by 8 (32).  16-bit rows fill all 64 banks, so
-// h sends each of the four rows to its own quarter of the banks and the two
-// groups to different halves of it; 8-bit rows fill half of the banks, so even
-// and odd rows never meet, and h spreads four row pairs and the two groups.
-template <int ES> struct PhaseT {
-  static constexpr int RB = 128 * ES;
-  static constexpr int NCH = RB / 16;
-  static __device__ __forceinline__ int h(int k) {
-    return ES == 2 ? (4 * (k & 3)) ^ (2 * ((k >> 3) & 1)) : (2 * ((k >> 1) & 3)) ^ ((k >> 5) & 1);
-  }
-  static __device__ __forceinline__ int addr(int k, int col) {
-    const int byte = col * ES;
-    return k * RB + (((byte >> 4) ^ h(k)) << 4) + (byte & 15);
-  }
-};
-
-// 16-row MFMA fragments: lane l covers row (column) l % 16 of the block and the
-// K bytes [ks*4*FB + (l/16)*FB, +FB) of the tile.  pk_lane / pt_lane are the
-// per-lane offsets at ks = 0; K step ks XORs 64*ks into the K-contiguous one
-// (16-bit tiles hold two steps, 8-bit tiles one) and adds 32 k-rows to the
-// k-major one.
-template <int ES> __device__ __forceinline__ int pk_lane(int lane, int e) {
-  const int r = lane & 15, g = lane >> 4;
-  const int c = ES == 2 ? g : 2 * g + e;
-  return r * 128 + ((c ^ ((r >> 1) & 7)) << 4);
-}
-template <int ES> __device__ __forceinline__ int pt_lane(int lane, int col0, int hh) {
-  const int L = lane & 15, kb = (lane >> 4) * (FragT<ES>::FB / ES);
-  if constexpr (ES == 2) return PhaseT<ES>::addr(kb + 4 * hh + (L >> 2), col0 + 4 * (L & 3));
-  else return PhaseT<ES>::addr(kb + 8 * hh + (L >> 1), col0 + 8 * (L & 1));
-}
-template <int ES>
-__device__ __forceinline__ typename FragT<ES>::T pk_frag(const lds_u8* blk, int o0, int o1, int ks) {
-  if constexpr (ES == 2) return lds_read16(blk + (o0 ^ (64 * ks)));
-  else return frag_k<1>(blk, o0, o1, 0);
-}
-template <int ES, int NHH>
-__device__ __forceinline__ typename FragT<ES>::T pt_frag(const lds_u8* tile, const int (&off)[NHH], int ks) {
-  return frag_t<ES, PhaseT<ES>>(tile + (ES == 2 ? ks * 32 * PhaseT<ES>::RB : 0), off, 0);
-}
 
 template <int DT> struct PCfg {
   static constexpr int ES = ElemSize<DT>::v;
@@ -126,8 +82,8 @@ template <int ES, bool KC> struct PhaseCopy {
           off[hf][j] = (row0 + hf * 128 + r) * ld_b + c * 16;
         } else {
           const int q = blk * 64 + lane;
-          const int k = q / PhaseT<ES>::NCH;
-          const int c = (q % PhaseT<ES>::NCH) ^ PhaseT<ES>::h(k);
+          const int k = q / TileT<ES, 128>::NCH;
+          const int c = (q % TileT<ES, 128>::NCH) ^ TileT<ES, 128>::h(k);
           off[hf][j] = k * ld_b + (row0 + hf * 128) * ES + c * 16;
         }
       }
@@ -149,44 +105,6 @@ template <int ES, bool KC> struct PhaseCopy {
   }
 };
 
-// The rounded BM x BN tile in LDS at `out` (rows of PITCH bytes) to C, all
-// threads of the workgroup: 16 bytes a lane, or single elements where C's rows
-// have no 8-byte alignment.  rows, cols: what of the tile lies inside C; off:
-// its first byte.
-template <int BN, int NT, int PITCH>
-__device__ __forceinline__ void store_tile(const lds_u8* out, Rsrc rc, int off, int ldc_b, int rows, int cols,
-                                           bool vec, int tid) {
-  constexpr int LPR = BN / 8;  // lanes per row
-  if (vec) {
-    const int c8 = (tid % LPR) * 8;
-    const int left = cols - c8;  // columns from this lane's first one
-#pragma unroll 4
-    for (int r = tid / LPR; r < rows; r += NT / LPR) {
-      const u32x4 v = lds_read16(out + r * PITCH + c8 * 2);
-      const int o = off + r * ldc_b + c8 * 2;
-      if (left >= 8) {
-        __builtin_amdgcn_raw_buffer_store_b128(v, rc, o, 0, 0);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (e < left)
-            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[e / 2] >> (16 * (e & 1))), rc, o + 2 * e, 0, 0);
-      }
-    }
-  } else {
-    const int lane = tid & 63;
-    for (int r = tid / 64; r < rows; r += NT / 64)
-#pragma unroll
-      for (int e = 0; e < BN / 64; ++e) {
-        const int c = e * 64 + lane;
-        if (c < cols)
-          __builtin_amdgcn_raw_buffer_store_b16(
-              *(const __attribute__((address_space(3))) uint16_t*)(out + r * PITCH + c * 2), rc,
-              off + r * ldc_b + c * 2, 0, 0);
-      }
-  }
-}
-
 template <int DT, int TA, int TB>
 __global__ void __launch_bounds__(512)
 go_gemm_p(KLaunch L) {
@@ -194,7 +112,8 @@ go_gemm_p(KLaunch L) {
   typedef Mma<DT, 16> M;
   typedef typename FragT<C::ES>::T Frag;
   typedef typename M::Acc Acc;
-  constexpr int NHH = C::ES == 2 ? 2 : 4;
+  typedef TileT<C::ES, 128> PT;  // a k-major half tile
+  constexpr int NHH = PT::NHH;
 
   __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[kPLds];
   lds_u8* smem = (lds_u8*)smem_raw;
@@ -225,13 +144,13 @@ go_gemm_p(KLaunch L) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int hh = 0; hh < NHH; ++hh) aoff[i][hh] = pt_lane<C::ES>(lane, wm * 64 + i * 16, hh);
+      for (int hh = 0; hh < NHH; ++hh) aoff[i][hh] = PT::lane_off(lane, wm * 64 + i * 16, hh);
   }
   if constexpr (TB == 0) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int hh = 0; hh < NHH; ++hh) boff[j][hh] = pt_lane<C::ES>(lane, wn * 32 + j * 16, hh);
+      for (int hh = 0; hh < NHH; ++hh) boff[j][hh] = PT::lane_off(lane, wn * 32 + j * 16, hh);
   }
 
   const int total = ntiles * p.batch;
@@ -264,7 +183,7 @@ go_gemm_p(KLaunch L) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if constexpr (TA == 0) af[ks][i] = pk_frag<C::ES>(S + (wm * 64 + i * 16) * 128, kc0, kc1, ks);
-          else af[ks][i] = pt_frag<C::ES>(S, aoff[i], ks);
+          else af[ks][i] = PT::frag(S, aoff[i], ks);
         }
     };
     auto read_b = [&](const lds_u8* S, int hf) {
@@ -273,7 +192,7 @@ go_gemm_p(KLaunch L) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           if constexpr (TB == 1) bf[hf][ks][j] = pk_frag<C::ES>(S + (wn * 32 + j * 16) * 128, kc0, kc1, ks);
-          else bf[hf][ks][j] = pt_frag<C::ES>(S, boff[j], ks);
+          else bf[hf][ks][j] = PT::frag(S, boff[j], ks);
         }
     };
     // the second half of a phase: swap with the other group, MFMAs, swap back

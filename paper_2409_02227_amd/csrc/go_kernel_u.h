@@ -1,10 +1,8 @@
-// go_kernel_u.h -- GO-Kernels for operands of any size and alignment (16-bit
-// and 8-bit types): the kernels the planner binds where K is no whole number of
-// K tiles, or a base, row pitch or item stride no multiple of 16 bytes.
+// go_kernel_u.h -- the GO-Kernels of the 16- and 8-bit types for tiles below
+// 256 x 256, and for operands of any size and alignment.
 //
-// Both operands lie in LDS as the buffer unit's direct copies leave them (the
-// swizzled layouts below), and each operand gets there by one of two ways,
-// chosen per GEMM:
+// Both operands lie in LDS in the layouts of lds_copy.h, and each gets there by
+// one of two ways, chosen per GEMM:
 //  * copies: base, pitch and item stride multiples of 16 bytes (and, for a
 //    K-contiguous operand, K whole 16-byte chunks): direct global -> LDS
 //    copies; chunks past K are sent out of range and read as zeros;
@@ -13,54 +11,25 @@
 //    with v_alignbit, zeroes what lies past K and writes the chunk to the same
 //    place of the same layout.  K-major operands stay k-major: the transpose
 //    is left to the LDS reads.
-// What bounds it: the kernels it replaced loaded unaligned operands element by
-// element (8 or 16 loads a chunk instead of 2) and transposed k-major operands
-// in registers.
+// The direct kernels (_dS) have the first way only, with a ring of S stages; the
+// others (_m32, _m16), which the planner binds where K is no whole number of K
+// tiles or an alignment is missing, have both and two stages.
 //
-// Two K tiles in LDS, one barrier per K tile: tile kt+1 goes to LDS while kt
-// is computed, and in the register way tile kt+2 is being loaded, so a load has
-// a whole tile's time to arrive.  16 x 16 MFMAs; the rounded tile leaves
-// through LDS as whole rows.
+// One barrier per K tile.  Direct: S - 1 tiles are in flight while one is
+// computed.  Both ways: tile kt+1 goes to LDS while kt is computed, and in the
+// register way tile kt+2 is being loaded, so a load has a whole tile's time to
+// arrive.  Waves read the fragments of a K step and issue its MFMAs; the other
+// workgroup of the CU fills the gaps (tiles of up to 64 KiB of LDS), which
+// beat prefetching fragments across the barrier within one: 4096^3 bf16 on
+// 128 x 128, two stages, 1107 against 1014 TFLOP/s.  16 x 16 MFMAs (less energy
+// a flop than 32 x 32); the rounded tile leaves through LDS as whole rows.
+// Unaligned operands, on the kernels with element loads and register
+// transposes before and on these: 2 x (509, 2047, 1021) fp16 on 64 x 64 tiles
+// 55 and 19 us; K tails, 2 x (1000, 2000, 1000) bf16 on 128 x 128: 31 and 18 us.
 #pragma once
 #include "go_kernel_p.h"
 
 namespace gdy {
-
-// k-major tile of ROWS elements per k-row: 16-byte chunk c of row k at position
-// c ^ h(k).  A transpose read takes, 32 lanes at a time, 16 columns of 4
-// (16-bit: two chunks) or 8 (8-bit: one chunk) consecutive k-rows for two
-// groups of lanes whose k differ by 8 (32).  Rows of 256 bytes and more all
-// start on bank 0, shorter ones on the bank their k gives; h spreads those that
-// share banks over different chunks (rows of 16 or 32 bytes, the transposed A
-// of 16-row tiles, keep their order: two lanes to a bank).
-template <int ES, int ROWS> struct TileT {
-  static constexpr int RB = ROWS * ES;
-  static constexpr int NCH = RB / 16;
-  static_assert(RB >= 16 && RB <= 512, "1 to 32 chunks per k-row");
-  static __device__ __forceinline__ int h(int k) {
-    if constexpr (RB < 64) {
-      return 0;
-    } else if constexpr (ES == 2) {
-      if constexpr (RB >= 256) return (4 * (k & 3)) ^ (2 * ((k >> 3) & 1));
-      else if constexpr (RB == 128) return (2 * ((k >> 1) & 1)) ^ (4 * ((k >> 3) & 1));
-      else return 2 * ((k >> 3) & 1);
-    } else {
-      if constexpr (RB >= 256) return (2 * (k & 7)) ^ ((k >> 5) & 1);
-      else if constexpr (RB == 128) return (2 * ((k >> 1) & 3)) ^ ((k >> 5) & 1);
-      else return (2 * ((k >> 2) & 1)) ^ ((k >> 5) & 1);
-    }
-  }
-  static __device__ __forceinline__ int addr(int k, int col) {
-    const int byte = col * ES;
-    return k * RB + (((byte >> 4) ^ h(k)) << 4) + (byte & 15);
-  }
-  // per-lane offset of sub-read hh of a 16-column fragment at K step 0
-  static __device__ __forceinline__ int lane_off(int lane, int col0, int hh) {
-    const int L = lane & 15, kb = (lane >> 4) * (FragT<ES>::FB / ES);
-    if constexpr (ES == 2) return addr(kb + 4 * hh + (L >> 2), col0 + 4 * (L & 3));
-    else return addr(kb + 8 * hh + (L >> 1), col0 + 8 * (L & 1));
-  }
-};
 
 // One operand of a tile: ROWS rows (or columns) x 128 bytes of K, KC:
 // K-contiguous.  Lane `lane` of wave `wave` owns the chunks at LDS bytes
@@ -153,7 +122,7 @@ template <int ES, bool KC, int ROWS, int NW> struct Operand {
   }
 };
 
-template <int DT, int BM, int BN, int WM, int WN> struct UCfg {
+template <int DT, int BM, int BN, int WM, int WN, int STAGES> struct UCfg {
   static constexpr int ES = ElemSize<DT>::v;
   static constexpr int BK = 128 / ES;
   static constexpr int NW = WM * WN;
@@ -162,21 +131,22 @@ template <int DT, int BM, int BN, int WM, int WN> struct UCfg {
   static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128;
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int PITCH = BN * 2 + 16;  // of the rounded tile: a half wave's 16 rows on distinct banks
-  static constexpr int LDS = 2 * STAGE > BM * PITCH ? 2 * STAGE : BM * PITCH;
+  static constexpr int LDS = STAGES * STAGE > BM * PITCH ? STAGES * STAGE : BM * PITCH;
   static_assert(BM % (WM * 16) == 0 && BN % (WN * 16) == 0, "wave tile must hold whole 16 x 16 blocks");
   static_assert(LDS <= 160 * 1024, "LDS budget");
 };
 
-template <int DT, int TA, int TB, int BM, int BN, int WM, int WN, bool SPLIT>
+template <int DT, int TA, int TB, int BM, int BN, int WM, int WN, int STAGES, bool ANY, bool SPLIT>
 __global__ void __launch_bounds__(WM * WN * 64)
 go_gemm_u(KLaunch L) {
-  typedef UCfg<DT, BM, BN, WM, WN> C;
+  static_assert(!ANY || STAGES == 2, "the register way is a tile ahead of two stages");
+  typedef UCfg<DT, BM, BN, WM, WN, STAGES> C;
   typedef Mma<DT, 16> M;
   typedef typename FragT<C::ES>::T Frag;
   typedef typename M::Acc Acc;
   typedef Operand<C::ES, TA == 0, BM, C::NW> OpA;
   typedef Operand<C::ES, TB == 1, BN, C::NW> OpB;
-  constexpr int NHH = C::ES == 2 ? 2 : 4;
+  constexpr int NHH = OpA::T::NHH;
   constexpr int WTM = BM / WM, WTN = BN / WN;
 
   __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[C::LDS];
@@ -198,7 +168,7 @@ go_gemm_u(KLaunch L) {
   const int ntiles = p.tiles_m * p.tiles_n;
   const int lda_b = (int)p.lda * C::ES, ldb_b = (int)p.ldb * C::ES, ldc_b = (int)p.ldc * 2;
   const int Mrows = (int)p.m, Ncols = (int)p.n;
-  const bool acopy = p.a_dma, bcopy = p.b_dma;
+  const bool acopy = !ANY || p.a_dma, bcopy = !ANY || p.b_dma;
   const int a_extent = TA == 0 ? (Mrows - 1) * lda_b + (int)p.k * C::ES : ((int)p.k - 1) * lda_b + Mrows * C::ES;
   const int b_extent = TB == 1 ? (Ncols - 1) * ldb_b + (int)p.k * C::ES : ((int)p.k - 1) * ldb_b + Ncols * C::ES;
 
@@ -253,56 +223,94 @@ go_gemm_u(KLaunch L) {
 #pragma unroll
         for (int r = 0; r < M::NACC; ++r) acc[j][i][r] = 0.f;
 
+    // the MFMAs of the K tile at As; `between` runs once the first fragments
+    // have been read
+    auto compute = [&](const lds_u8* As, auto between) {
+      const lds_u8* Bs = As + C::A_BYTES;
+#pragma unroll
+      for (int ks = 0; ks < C::NKS; ++ks) {
+        Frag af[C::FM], bf[C::FN];
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j) {
+          if constexpr (TB == 1) bf[j] = pk_frag<C::ES>(Bs + (wn * WTN + j * 16) * 128, kc0, kc1, ks);
+          else bf[j] = OpB::T::frag(Bs, boff[j], ks);
+        }
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i) {
+          if constexpr (TA == 0) af[i] = pk_frag<C::ES>(As + (wm * WTM + i * 16) * 128, kc0, kc1, ks);
+          else af[i] = OpA::T::frag(As, aoff[i], ks);
+        }
+        if (ks == 0) between();
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+          for (int i = 0; i < C::FM; ++i) acc[j][i] = M::run(bf[j], af[i], acc[j][i]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // Past this barrier the tile whose copies the wave has waited for is in LDS
+    // for every wave, and every wave's reads of the tile before are done.
+    auto sync = [&]() {
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      __builtin_amdgcn_sched_barrier(0);
+      barrier_nowait();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto copy_tile = [&](int kt, int stage) {
+      lds_u8* st = smem + stage * C::STAGE;
+      oa.copy(kt, K * C::ES, st, wave);
+      ob.copy(kt, K * C::ES, st + C::A_BYTES, wave);
+    };
+
     if (nk > 0) {
-      // tile kt to its stage (register way: the values loaded before), and the
-      // loads of the tile after it
-      auto stage_in = [&](int kt) {
-        lds_u8* st = smem + (kt & 1) * C::STAGE;
-        if (acopy) {
-          oa.copy(kt, K * C::ES, st, wave);
-        } else {
-          oa.store(kt, K, st, wave, lane);
-          if (kt + 1 < nk) oa.load(kt + 1, wave);
-        }
-        if (bcopy) {
-          ob.copy(kt, K * C::ES, st + C::A_BYTES, wave);
-        } else {
-          ob.store(kt, K, st + C::A_BYTES, wave, lane);
-          if (kt + 1 < nk) ob.load(kt + 1, wave);
-        }
-      };
-      if (!acopy) oa.load(0, wave);
-      if (!bcopy) ob.load(0, wave);
-      stage_in(0);
-      for (int kt = 0; kt < nk; ++kt) {
-        // this wave's part of tile kt is in LDS and its reads of tile kt-1 are
-        // done; past the barrier that holds for every wave
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-        __builtin_amdgcn_sched_barrier(0);
-        barrier_nowait();
-        __builtin_amdgcn_sched_barrier(0);
-        const lds_u8* As = smem + (kt & 1) * C::STAGE;
-        const lds_u8* Bs = As + C::A_BYTES;
-#pragma unroll
-        for (int ks = 0; ks < C::NKS; ++ks) {
-          Frag af[C::FM], bf[C::FN];
-#pragma unroll
-          for (int j = 0; j < C::FN; ++j) {
-            if constexpr (TB == 1) bf[j] = pk_frag<C::ES>(Bs + (wn * WTN + j * 16) * 128, kc0, kc1, ks);
-            else bf[j] = frag_t<C::ES, typename OpB::T>(Bs + (C::ES == 2 ? ks * 32 * OpB::T::RB : 0), boff[j], 0);
+      if constexpr (ANY) {
+        // tile kt to its stage (register way: the values loaded before), and
+        // the loads of the tile after it
+        auto stage_in = [&](int kt) {
+          lds_u8* st = smem + (kt & 1) * C::STAGE;
+          if (acopy) {
+            oa.copy(kt, K * C::ES, st, wave);
+          } else {
+            oa.store(kt, K, st, wave, lane);
+            if (kt + 1 < nk) oa.load(kt + 1, wave);
           }
-#pragma unroll
-          for (int i = 0; i < C::FM; ++i) {
-            if constexpr (TA == 0) af[i] = pk_frag<C::ES>(As + (wm * WTM + i * 16) * 128, kc0, kc1, ks);
-            else af[i] = frag_t<C::ES, typename OpA::T>(As + (C::ES == 2 ? ks * 32 * OpA::T::RB : 0), aoff[i], 0);
+          if (bcopy) {
+            ob.copy(kt, K * C::ES, st + C::A_BYTES, wave);
+          } else {
+            ob.store(kt, K, st + C::A_BYTES, wave, lane);
+            if (kt + 1 < nk) ob.load(kt + 1, wave);
           }
-          if (ks == 0 && kt + 1 < nk) stage_in(kt + 1);
+        };
+        if (!acopy) oa.load(0, wave);
+        if (!bcopy) ob.load(0, wave);
+        stage_in(0);
+        for (int kt = 0; kt < nk; ++kt) {
+          wait_vmcnt<0>();
+          sync();
+          compute(smem + (kt & 1) * C::STAGE, [&]() {
+            if (kt + 1 < nk) stage_in(kt + 1);
+          });
+        }
+      } else {
+        // ring: STAGES - 1 tiles in flight while one is computed
+        constexpr int PER = OpA::N + OpB::N;  // copies of a wave per tile
+        static_assert(OpA::ALL && OpB::ALL && (STAGES - 2) * PER < 64, "counted copies");
+        wait_vmcnt<0>();  // the previous tile's stores
 #pragma unroll
-          for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-            for (int i = 0; i < C::FM; ++i) acc[j][i] = M::run(bf[j], af[i], acc[j][i]);
-          __builtin_amdgcn_sched_barrier(0);
+        for (int s = 0; s < STAGES - 1; ++s)
+          if (s < nk) copy_tile(s, s);
+        int cur = 0, free = STAGES - 1;  // stages of tile kt and of tile kt + STAGES - 1
+        for (int kt = 0; kt < nk; ++kt) {
+          const int after = min(STAGES - 2, nk - 1 - kt);  // tiles issued after tile kt
+          if (STAGES >= 4 && after >= 2) wait_vmcnt<(STAGES >= 4 ? 2 * PER : 0)>();
+          else if (STAGES >= 3 && after >= 1) wait_vmcnt<(STAGES >= 3 ? PER : 0)>();
+          else wait_vmcnt<0>();
+          sync();
+          compute(smem + cur * C::STAGE, [&]() {
+            if (kt + STAGES - 1 < nk) copy_tile(kt + STAGES - 1, free);
+          });
+          cur = cur + 1 == STAGES ? 0 : cur + 1;
+          free = free + 1 == STAGES ? 0 : free + 1;
         }
       }
     }
@@ -352,11 +360,17 @@ go_gemm_u(KLaunch L) {
 
 }  // namespace gdy
 
-// Catalogue entries, under the names of the register-staged family (same tiles;
-// the suffix named its MFMA block).
-#define GDY_KERNEL_U(DT, DTNAME, TA, TB, LAYOUT, BM, BN, WM, WN, MM)                              \
-  {DTNAME "_" LAYOUT "_" #BM "x" #BN "_w" #WM "x" #WN "_m" #MM,                                    \
-   DT, TA, TB, BM, BN, ::gdy::UCfg<DT, BM, BN, WM, WN>::BK, WM * WN,                               \
-   16, ::gdy::UCfg<DT, BM, BN, WM, WN>::LDS,                                                        \
-   reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, false>), 0, 0,       \
-   reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, true>)}
+// Catalogue entries.  _m32 / _m16: any operands (the names are those of the
+// register-staged family, whose MFMA block they gave); _dS: direct copies only,
+// S stages.
+#define GDY_KERNEL_UX(DT, TA, TB, BM, BN, WM, WN, ST, ANY, DIRECT, NAME)                              \
+  {NAME, DT, TA, TB, BM, BN, ::gdy::UCfg<DT, BM, BN, WM, WN, ST>::BK, WM * WN, 16,                   \
+   ::gdy::UCfg<DT, BM, BN, WM, WN, ST>::LDS,                                                          \
+   reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, ST, ANY, false>), DIRECT, 0, \
+   reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, ST, ANY, true>)}
+#define GDY_KERNEL_U(DT, DTNAME, TA, TB, LAYOUT, BM, BN, WM, WN, MM)                                  \
+  GDY_KERNEL_UX(DT, TA, TB, BM, BN, WM, WN, 2, true, 0,                                               \
+                DTNAME "_" LAYOUT "_" #BM "x" #BN "_w" #WM "x" #WN "_m" #MM)
+#define GDY_KERNEL_D(DT, DTNAME, TA, TB, LAYOUT, BM, BN, WM, WN, ST)                                  \
+  GDY_KERNEL_UX(DT, TA, TB, BM, BN, WM, WN, ST, false, 1,                                             \
+                DTNAME "_" LAYOUT "_" #BM "x" #BN "_w" #WM "x" #WN "_d" #ST)

@@ -1,5 +1,5 @@
 // Direct GO-Kernel instantiations for bf16 inputs (fp32 accumulate, bf16 out).
-#include "go_kernel_p.h"
+#include "go_kernel_u.h"
 #define GDY_DT ::gdy::DT_BF16
 #define GDY_DTNAME "bf16"
 #define GDY_DT16 1

@@ -1,5 +1,5 @@
 // Direct GO-Kernel instantiations for fp16 inputs (fp32 accumulate, fp16 out).
-#include "go_kernel_p.h"
+#include "go_kernel_u.h"
 #define GDY_DT ::gdy::DT_F16
 #define GDY_DTNAME "f16"
 #define GDY_DT16 1

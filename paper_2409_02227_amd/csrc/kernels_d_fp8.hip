@@ -1,5 +1,5 @@
 // Direct GO-Kernel instantiations for OCP e4m3 inputs (fp32 accumulate, scaled, bf16 out).
-#include "go_kernel_p.h"
+#include "go_kernel_u.h"
 #define GDY_DT ::gdy::DT_FP8
 #define GDY_DTNAME "fp8"
 #define GDY_DT16 0

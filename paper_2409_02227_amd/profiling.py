@@ -64,7 +64,7 @@ PASSES = {
 COPY_BYTES = 1 << 30
 # what the kernels' HBM traffic depends on: the kernels, the launch block and
 # work mapping they share with the host, and the planner that fills it
-KERNEL_SOURCES = [os.path.join(HERE, "csrc", f) for f in ("go_kernel.h", "go_kernel_d.h", "go_kernel_p.h", "go_kernel_u.h", "gdy_internal.h",
+KERNEL_SOURCES = [os.path.join(HERE, "csrc", f) for f in ("go_kernel.h", "lds_copy.h", "go_kernel_p.h", "go_kernel_u.h", "gdy_internal.h",
                                                          "gdy.cpp")]
 
 
