@@ -104,8 +104,12 @@ typedef enum {
  * hardware queue switch costs tens of microseconds on MI355X, far more than
  * the small GEMMs of a group take, so the concurrency of a group lives in one
  * grid wherever its kernels allow.  Each tile is computed by the same code as
- * in an isolated launch, so results are bit-identical.  SEQUENTIAL, DEFAULT
- * and FORCED launch one dispatch per GEMM.
+ * in an isolated launch, so results are bit-identical.  In GO and SELECTOR,
+ * dispatches of a group whose kernels belong to one family (256 x 256 tiles;
+ * smaller ones) and input type run jointly in one kernel launch, each GEMM on
+ * the code of its own kernel, with the same bits: the plan still counts a
+ * dispatch per kernel, and they share a stream slot and, in the timings, an
+ * interval.  SEQUENTIAL, DEFAULT and FORCED launch one dispatch per GEMM.
  */
 #define GDY_MAX_FUSED 16
 
@@ -313,7 +317,8 @@ gdy_status gdy_kernel_times(gdy_ctx* ctx, int32_t back, float* start_ms, float* 
  * Dispatch map (host only; works on host-only contexts): plans the
  * submission as gdy_plan does, builds launch block `dispatch` of the plan
  * as gdy_execute would, and reports what each of its workgroups computes,
- * with the kernels' own mapping code.  *grid receives the dispatch's
+ * with the kernels' own mapping code (workgroups of other dispatches that run
+ * jointly with it are reported idle).  *grid receives the launch's
  * workgroup count; for workgroup b < min(*grid, max_workgroups),
  * gemm_of_wg[b] is the submission index of the member it serves (-1: an
  * idle workgroup) and it runs that member's work items first_item[b],

@@ -44,6 +44,7 @@ const int kSplitMaxTile = 128 * 128;           // larger tiles' split twins spil
 
 struct Kernel {
   const KernelDesc* d;
+  const void* func;  // d->func, or the direct kernel's of the same tile
   int code;       // index of the first catalogue entry that runs the same code
   int occupancy;  // workgroups per CU
   int vgprs;
@@ -662,6 +663,65 @@ bool is_add_variant(const gdy_ctx* ctx, int vid) {
 // code (several names may run one kernel).
 int code_of(const gdy_ctx* ctx, int vid) { return ctx->kernels[ctx->variants[vid].kernel].code; }
 
+// Direct copies to LDS move 16-byte chunks: the base, the row pitch and the
+// item stride must be multiples of 16 bytes.  A K-contiguous operand's K must
+// be whole chunks (chunks past K read as zeros); k-major rows past K lie past
+// the extent and read as zeros whatever K is.
+bool copies_ok(const void* ptr, int64_t ld, int64_t k, int es, bool kcontiguous, int64_t item_stride) {
+  return (uintptr_t)ptr % 16 == 0 && (ld * es) % 16 == 0 && (item_stride * es) % 16 == 0 &&
+         (!kcontiguous || (k * es) % 16 == 0);
+}
+
+bool a_copies(const gdy_gemm& g) {
+  return copies_ok(g.a, g.lda, g.k, elem_size(g.a_type), g.trans_a == 0, g.batch > 1 ? g.stride_a : 0);
+}
+bool b_copies(const gdy_gemm& g) {
+  return copies_ok(g.b, g.ldb, g.k, elem_size(g.a_type), g.trans_b == 1, g.batch > 1 ? g.stride_b : 0);
+}
+
+const void* joint_kernel(int dtype, int family) {
+  return dtype == DT_BF16 ? joint_bf16(family) : dtype == DT_F16 ? joint_f16(family)
+         : dtype == DT_FP8 ? joint_fp8(family) : nullptr;
+}
+
+// How a GEMM (or add) runs on a variant: its kernel, and the family, member
+// code and tile of a joint launch (family 0: none takes it).  The 256 x 256
+// kernel for any operands is the alternating one where both take copies; other
+// GEMMs run as 128 x 128 tiles of the joint kernel, alone too.
+struct Exec {
+  const void *func, *func_split;
+  int waves, bm, bn;        // of its own launch
+  int family, code, jbm, jbn;
+  int key;                  // GEMMs of one key may share an own launch
+};
+
+Exec exec_of(const gdy_ctx* ctx, int vid, const gdy_gemm& g) {
+  const Kernel& k = ctx->kernels[ctx->variants[vid].kernel];
+  const KernelDesc* d = k.d;
+  Exec e = {k.func, d->func_split, d->waves, d->bm, d->bn, d->joint, d->joint_code, d->joint_bm, d->joint_bn, 2 * k.code};
+  if (d->joint == 2 && !d->direct && !(a_copies(g) && b_copies(g))) {
+    e.func = e.func_split = joint_kernel(d->dtype, 1);
+    e.waves = 4;
+    e.bm = e.bn = e.jbm = e.jbn = 128;
+    e.family = 1;
+    e.code = (2 * d->ta + d->tb) * 8;
+    e.key = 2 * ctx->variants[vid].kernel + 1;
+  }
+  return e;
+}
+
+// As a member of a joint launch of `family`: 256 x 256 kernels join 128 x 128
+// ones as 128 x 128 tiles.
+Exec joint_exec(const gdy_ctx* ctx, int vid, const gdy_gemm& g, int family) {
+  Exec e = exec_of(ctx, vid, g);
+  if (family == 1 && e.family == 2) {
+    e.code *= 8;
+    e.jbm = e.jbn = 128;
+    e.family = 1;
+  }
+  return e;
+}
+
 // Dispatches of one group (members in launch order, GEMMs before adds,
 // variants bound): GEMMs of the same kernel share a dispatch, at most
 // kMaxFused each, numbered in order of first use.  An element-wise add
@@ -670,12 +730,12 @@ int code_of(const gdy_ctx* ctx, int vid) { return ctx->kernels[ctx->variants[vid
 // stream); otherwise adds of one type share an add dispatch.  The group's
 // first dispatch runs on the origin stream, the others round-robin on the
 // pool.
-void form_dispatches(const gdy_ctx* ctx, const std::vector<int>& members, int S, gdy_plan_t* p) {
+void form_dispatches(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<int>& members, int S, gdy_plan_t* p) {
   std::vector<int> kern, id, cnt;
   for (int i : members) {
-    const int k = code_of(ctx, p->variant_of[i]);
+    const int k = exec_of(ctx, p->variant_of[i], g[i]).key;
     int d = -1;
-    if (is_add_variant(ctx, p->variant_of[i]) && !kern.empty() && !ctx->kernels[kern[0]].d->ew &&
+    if (is_add_variant(ctx, p->variant_of[i]) && !kern.empty() && !ctx->kernels[kern[0] / 2].d->ew &&
         cnt[0] < kMaxFused)
       d = 0;
     else
@@ -827,7 +887,7 @@ void plan_splits(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode)
     p->group_size[q] = (int)grp.size();
     for (int i : grp) p->group_of[i] = q;
     if (grouped_mode(mode)) {
-      form_dispatches(ctx, grp, S, p);
+      form_dispatches(ctx, g, grp, S, p);
     } else {  // one dispatch per GEMM on its planned stream (partition, pool slot)
       for (int i : grp) p->dispatch_of[i] = p->n_dispatches++;
     }
@@ -865,11 +925,13 @@ void plan_splits(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode)
 
 void make_plan_core(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int forced_cd,
                     gdy_plan_t* p);
+void plan_units(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode);
 
 void make_plan(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int forced_cd,
                gdy_plan_t* p) {
   make_plan_core(ctx, g, n, mode, forced_cd, p);
   plan_splits(ctx, g, p, mode);
+  plan_units(ctx, g, p, mode);
 }
 
 void make_plan_core(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int forced_cd,
@@ -971,7 +1033,7 @@ void make_plan_core(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int 
       p->group_size[q] = (int)grp.size();
       p->n_groups = q + 1;
       p->cd = std::max(p->cd, (int)grp.size());
-      form_dispatches(ctx, grp, S, p);
+      form_dispatches(ctx, g, grp, S, p);
     }
     p->fallback = (mode == GDY_GO && (fb || !ctx->table.loaded)) ? 1 : 0;
     return;
@@ -1094,7 +1156,7 @@ void make_plan_core(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int 
       p->order[t++] = i;
       p->group_of[i] = q;
     }
-    form_dispatches(ctx, ordered, S, p);
+    form_dispatches(ctx, g, ordered, S, p);
   }
   p->fallback = fb ? 1 : 0;
 }
@@ -1108,15 +1170,6 @@ bool vec_ok(const void* ptr, int64_t ld, int es, bool kcontiguous, int64_t item_
   const uintptr_t a = (uintptr_t)ptr;
   const int64_t v = (kcontiguous || es >= 2) ? 16 : 8;  // fp8 k-major operand: 8-byte row vectors
   return a % v == 0 && (ld * es) % v == 0 && item_stride_bytes % v == 0;
-}
-
-// Direct copies to LDS move 16-byte chunks: the base, the row pitch and the
-// item stride must be multiples of 16 bytes.  A K-contiguous operand's K must
-// be whole chunks (chunks past K read as zeros); k-major rows past K lie past
-// the extent and read as zeros whatever K is.
-bool copies_ok(const void* ptr, int64_t ld, int64_t k, int es, bool kcontiguous, int64_t item_stride) {
-  return (uintptr_t)ptr % 16 == 0 && (ld * es) % 16 == 0 && (item_stride * es) % 16 == 0 &&
-         (!kcontiguous || (k * es) % 16 == 0);
 }
 
 // Buffer size for reads: the extent rounded up to the end of the dword that
@@ -1165,8 +1218,8 @@ KArgs make_args(const gdy_ctx* ctx, int vid, const gdy_gemm& g, Geometry* geo_ou
   a.b_vec = (g.k > 0 || add) && vec_ok(g.b, g.ldb, es, add || g.trans_b == 1, batched ? g.stride_b * es : 0);
   a.c_vec = (uintptr_t)g.c % 8 == 0 && (g.ldc * out_size(g)) % 8 == 0 &&
             (!batched || (g.stride_c * out_size(g)) % 8 == 0);
-  a.a_dma = copies_ok(g.a, g.lda, g.k, es, g.trans_a == 0, batched ? g.stride_a : 0);
-  a.b_dma = copies_ok(g.b, g.ldb, g.k, es, g.trans_b == 1, batched ? g.stride_b : 0);
+  a.a_dma = a_copies(g);
+  a.b_dma = b_copies(g);
   a.group_m = 8;
   a.xcd_remap = 1;
   a.batch = (int32_t)std::max(g.batch, 1);
@@ -1194,40 +1247,51 @@ bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, cons
 // its cap x occupancy), every range but the last rounded up to a multiple
 // of 8 so each GEMM starts on XCD 0 (the extra workgroups find no tile).
 gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p,
-                        const std::vector<int>& members, const std::vector<int64_t>& ws_off,
+                        const std::vector<int>& members, int joint, const std::vector<int64_t>& ws_off,
                         float* ws_base, int64_t ws_cap, KLaunch* L, int* grid, bool* split) {
   std::memset(L, 0, sizeof *L);
   L->count = (int)members.size();
   *split = false;
   int64_t wg = 0;
+  bool one_tile = true;  // every member runs the same tile
+  int tile_m = 0, tile_n = 0;
   for (int u = 0; u < L->count; ++u) {
     const int i = members[u];
-    Geometry geo;
-    L->g[u] = make_args(ctx, p.variant_of[i], g[i], &geo);
+    const Variant& v = ctx->variants[p.variant_of[i]];
+    const KernelDesc* d = ctx->kernels[v.kernel].d;
+    const Exec e = joint ? joint_exec(ctx, p.variant_of[i], g[i], joint) : exec_of(ctx, p.variant_of[i], g[i]);
+    KArgs& a = L->g[u];
+    a = make_args(ctx, p.variant_of[i], g[i], nullptr);
+    if (!d->ew) {
+      const int bm = joint ? e.jbm : e.bm, bn = joint ? e.jbn : e.bn;
+      if (tile_m == 0) tile_m = bm, tile_n = bn;
+      if (tile_m != bm || tile_n != bn) one_tile = false;
+      a.tiles_m = (int32_t)((g[i].m + bm - 1) / bm);
+      a.tiles_n = (int32_t)((g[i].n + bn - 1) / bn);
+      a.code = e.code;
+    }
+    const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n * a.batch;
+    const int64_t cap = v.cap > 0 ? (int64_t)v.cap * std::max(ctx->kernels[v.kernel].occupancy, 1) : INT32_MAX;
     L->first[u] = (int32_t)wg;
-    int span = std::max(geo.grid, 1);
+    int64_t span = std::max<int64_t>(std::min(tiles, cap), 1);
     const int s = std::max(p.split_of[i], 1);
     if (s > 1) {  // every tile in s K runs; a capped variant keeps its cap
-      const Variant& v = ctx->variants[p.variant_of[i]];
-      const KernelDesc* d = ctx->kernels[v.kernel].d;
       if (!ws_base || ws_off[i] < 0 || ws_off[i] + split_ws_bytes(g[i], s) > ws_cap)
         return fail(ctx, GDY_ERR_UNSUPPORTED, "gemm %d: split-K workspace exhausted", i);
       const int64_t nk = (g[i].k + d->bk - 1) / d->bk;
-      L->g[u].split = s;
-      L->g[u].split_kt = (int32_t)((nk + s - 1) / s);
-      L->g[u].ws = ws_base + ws_off[i] / 4;
-      span = (int)std::min<int64_t>((int64_t)geo.tiles * s,
-                                    v.cap > 0 ? (int64_t)v.cap * std::max(ctx->kernels[v.kernel].occupancy, 1)
-                                              : INT32_MAX);
+      a.split = s;
+      a.split_kt = (int32_t)((nk + s - 1) / s);
+      a.ws = ws_base + ws_off[i] / 4;
+      span = std::min<int64_t>(tiles * s, cap);
       *split = true;
     }
-    if (u + 1 < L->count) span = (span + 7) & ~7;
+    if (u + 1 < L->count) span = (span + 7) & ~7LL;
     wg += span;
   }
   if (wg > INT32_MAX) return fail(ctx, GDY_ERR_UNSUPPORTED, "dispatch grid of %lld workgroups", (long long)wg);
   L->first[L->count] = (int32_t)wg;
   *grid = (int)wg;
-  if (!*split) place_xcds(ctx, g, p, members, L, grid);
+  if (!*split && one_tile) place_xcds(ctx, g, p, members, L, grid);
   return GDY_OK;
 }
 
@@ -1381,6 +1445,106 @@ std::vector<int> dispatch_members(const gdy_plan_t& p, int d) {
   return out;
 }
 
+// One kernel launch: a dispatch, or several dispatches of a group (each GEMM
+// on the kernel the plan names) run jointly in one grid.
+struct Unit {
+  std::vector<int> ids;      // its dispatches
+  std::vector<int> members;  // their GEMMs and adds, launch order
+  int joint = 0;             // its family, 0: one dispatch on its own kernel
+};
+
+// The launches of one group's dispatches (ids, in launch order, and their
+// members).  In the modes that choose kernels by group, dispatches whose kernels
+// belong to one family and input type join the first of them that has room
+// (kMaxFused members): see go_gemm_joint.  Grid-capped kernels keep launches of
+// their own (their cap counts workgroups of their own occupancy).
+// A group's 256 x 256 kernels run
+// apart from its smaller ones (512 threads a workgroup, all of the LDS), unless
+// they are short: as 128 x 128 tiles of the joint launch they take about a
+// quarter longer (4096^3 bf16: 124 us, 100 on 256 x 256), a fork and join
+// 20-25 us, so below kJoinUs of roofline time they join.
+const double kJoinUs = 40.0;
+std::vector<Unit> launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
+                               const std::vector<int>& ids, const std::vector<std::vector<int>>& members) {
+  std::vector<Unit> out;
+  std::vector<int> family(ids.size(), 0), dtype(ids.size(), 0);
+  double large_s = 0.0;
+  for (size_t u = 0; u < ids.size(); ++u) {
+    bool capped = false;
+    for (int i : members[u]) {
+      if (is_add_variant(ctx, p.variant_of[i])) continue;
+      family[u] = exec_of(ctx, p.variant_of[i], g[i]).family;
+      dtype[u] = g[i].a_type;
+      if (ctx->variants[p.variant_of[i]].cap > 0) capped = true;
+      if (family[u] == 2) large_s += roofline_s(g[i]);
+    }
+    if (capped || (mode != GDY_SELECTOR && mode != GDY_GO)) family[u] = 0;
+  }
+  if (large_s < kJoinUs * 1e-6)
+    for (size_t u = 0; u < ids.size(); ++u)
+      for (size_t q = 0; q < ids.size(); ++q)
+        if (family[u] == 2 && family[q] == 1 && dtype[q] == dtype[u]) family[u] = 1;
+  std::vector<size_t> first;  // the dispatch that opened each launch
+  for (size_t u = 0; u < ids.size(); ++u) {
+    size_t q = 0;
+    while (q < out.size() && !(family[u] > 0 && family[first[q]] == family[u] && dtype[first[q]] == dtype[u] &&
+                               out[q].members.size() + members[u].size() <= (size_t)kMaxFused))
+      ++q;
+    if (q == out.size()) {
+      out.emplace_back();
+      first.push_back(u);
+    } else {
+      out[q].joint = family[u];
+    }
+    out[q].ids.push_back(ids[u]);
+    out[q].members.insert(out[q].members.end(), members[u].begin(), members[u].end());
+  }
+  // the longest work items first, as within a dispatch; adds last
+  for (Unit& x : out)
+    if (x.joint) {
+      auto item = [&](int i) {
+        const Exec e = joint_exec(ctx, p.variant_of[i], g[i], x.joint);
+        return g[i].k / std::max(p.split_of[i], 1) * e.jbm * e.jbn;
+      };
+      std::stable_sort(x.members.begin(), x.members.end(), [&](int a, int b) {
+        const bool ea = g[a].op == GDY_OP_ADD, eb = g[b].op == GDY_OP_ADD;
+        return ea || eb ? !ea && eb : item(a) > item(b);
+      });
+    }
+  return out;
+}
+
+// The dispatches of group grp (launch order) and their members.
+void group_dispatches(const gdy_plan_t& p, int grp, std::vector<int>* ids, std::vector<std::vector<int>>* members) {
+  for (int t = 0; t < GDY_MAX_GEMMS && p.order[t] >= 0; ++t) {
+    const int i = p.order[t];
+    if (p.group_of[i] != grp) continue;
+    size_t u = 0;
+    while (u < ids->size() && (*ids)[u] != p.dispatch_of[i]) ++u;
+    if (u == ids->size()) {
+      ids->push_back(p.dispatch_of[i]);
+      members->emplace_back();
+    }
+    (*members)[u].push_back(i);
+  }
+}
+
+// Streams of the joint modes' launches: a group's first launch on the origin
+// stream, the others round-robin on the pool.
+void plan_units(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode) {
+  if ((mode != GDY_SELECTOR && mode != GDY_GO) || p->n_dispatches <= p->n_groups) return;
+  const int S = std::max(pool_size(ctx), 1);
+  for (int grp = 0; grp < p->n_groups; ++grp) {
+    std::vector<int> ids;
+    std::vector<std::vector<int>> members;
+    group_dispatches(*p, grp, &ids, &members);
+    if (ids.size() < 2) continue;
+    const std::vector<Unit> units = launch_units(ctx, g, *p, mode, ids, members);
+    for (size_t u = 0; u < units.size(); ++u)
+      for (int i : units[u].members) p->stream_of[i] = u == 0 ? -1 : (int)(u - 1) % S;
+  }
+}
+
 gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
                        hipStream_t origin, float* ws_base, int64_t ws_cap) {
   gdy_status st = GDY_OK;
@@ -1394,8 +1558,6 @@ gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
   auto stream_at = [&](int s) { return parted ? ctx->parts[pr][s] : slot_stream(ctx, s); };
   auto done_at = [&](int s) { return parted ? ctx->part_done[pr][s] : ctx->done[s]; };
   const std::vector<int64_t> ws_off = ws_offsets(g, p, mode);
-  int L = 0;
-  while (L < GDY_MAX_GEMMS && p.order[L] >= 0) ++L;
   const int D = p.n_dispatches;
   TimingSlot* ts = nullptr;
   if (ctx->timing) {
@@ -1415,65 +1577,60 @@ gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
     HIP_TRY(ctx, hipEventRecord(ts->sub_start, origin));
   }
 
-  // launch order is p.order; groups are contiguous in it, and so are the
-  // members of a dispatch once its first member has appeared
-  int t = 0;
   for (int grp = 0; grp < p.n_groups && st == GDY_OK; ++grp) {
-    std::vector<int> ids;                    // dispatches of this group, launch order
-    std::vector<std::vector<int>> members;  // their GEMMs
-    std::vector<int> slots;                  // pool slots the group uses
-    for (; t < L && p.group_of[p.order[t]] == grp; ++t) {
-      const int i = p.order[t];
-      const int d = p.dispatch_of[i];
-      size_t u = 0;
-      while (u < ids.size() && ids[u] != d) ++u;
-      if (u == ids.size()) {
-        ids.push_back(d);
-        members.emplace_back();
-        const int s = p.stream_of[i];
-        if (s >= 0 && std::find(slots.begin(), slots.end(), s) == slots.end()) slots.push_back(s);
-      }
-      members[u].push_back(i);
+    std::vector<int> ids;
+    std::vector<std::vector<int>> members;
+    group_dispatches(p, grp, &ids, &members);
+    const std::vector<Unit> units = launch_units(ctx, g, p, mode, ids, members);
+    std::vector<int> slots;  // pool slots the group uses
+    for (const Unit& x : units) {
+      const int s = p.stream_of[x.members[0]];
+      if (s >= 0 && std::find(slots.begin(), slots.end(), s) == slots.end()) slots.push_back(s);
     }
     // fork: pool streams start after what the origin holds
     if (!slots.empty()) {
       HIP_TRY(ctx, hipEventRecord(ctx->fork_ev, origin));
       for (int s : slots) HIP_TRY(ctx, hipStreamWaitEvent(stream_at(s), ctx->fork_ev, 0));
     }
-    for (size_t u = 0; u < ids.size(); ++u) {
-      int i0 = members[u][0];  // the dispatch runs its first GEMM's kernel (adds ride along)
-      for (int i : members[u])
+    for (const Unit& x : units) {
+      int i0 = x.members[0];  // the launch runs its first GEMM's kernel (adds ride along)
+      for (int i : x.members)
         if (!is_add_variant(ctx, p.variant_of[i])) {
           i0 = i;
           break;
         }
       const int vid = p.variant_of[i0];
-      const Kernel& k = ctx->kernels[ctx->variants[vid].kernel];
+      const Exec ex = exec_of(ctx, vid, g[i0]);
       KLaunch launch;
       int grid = 0;
       bool split = false;
-      st = build_launch(ctx, g, p, members[u], ws_off, ws_base, ws_cap, &launch, &grid, &split);
+      st = build_launch(ctx, g, p, x.members, x.joint, ws_off, ws_base, ws_cap, &launch, &grid, &split);
       if (st != GDY_OK) break;
       void* argv[] = {&launch};
-      const int d = ids[u];
+      const int d = x.ids[0];
+      const void* func = x.joint ? joint_kernel(g[i0].a_type, x.joint) : split ? ex.func_split : ex.func;
+      const int waves = !x.joint ? ex.waves : x.joint == 1 ? 4 : 8;
       hipStream_t hs = p.stream_of[i0] >= 0 ? stream_at(p.stream_of[i0]) : origin;
-      hipError_t e = hipExtLaunchKernel(split ? k.d->func_split : k.d->func, dim3(grid), dim3(k.d->waves * 64), argv, 0, hs,
+      hipError_t e = hipExtLaunchKernel(func, dim3(grid), dim3(waves * 64), argv, 0, hs,
                                         ts ? ts->start[d] : nullptr, ts && !split ? ts->stop[d] : nullptr, 0);
       if (e == hipSuccess && split) {
         // the split members' planes summed into C, on the same stream
         KLaunch red;
         int rgrid = 0;
-        build_reduce(ctx, g, p, members[u], launch, &red, &rgrid);
+        build_reduce(ctx, g, p, x.members, launch, &red, &rgrid);
         void* rargv[] = {&red};
         e = hipExtLaunchKernel(split_reduce_kernel(g[i0].c_type), dim3(rgrid), dim3(256), rargv, 0, hs, nullptr,
                                ts ? ts->stop[d] : nullptr, 0);
       }
       if (e != hipSuccess) {
         st = fail(ctx, GDY_ERR_HIP, "launch of %s (%d GEMMs, first %d) failed: %s",
-                  ctx->variants[vid].name.c_str(), (int)members[u].size(), i0, hipGetErrorString(e));
+                  ctx->variants[vid].name.c_str(), (int)x.members.size(), i0, hipGetErrorString(e));
         break;
       }
-      if (ts) ts->launched[d] = 1;
+      if (ts) {  // the dispatches of a joint launch report its interval
+        ts->launched[d] = 1;
+        for (int i : x.members) ts->dispatch_of[i] = d;
+      }
     }
     // join: the origin continues after the group's pool streams
     for (int s : slots) {
@@ -1698,21 +1855,29 @@ static gdy_status create_impl(gdy_ctx* ctx, int device, const char* table_path, 
     for (int i = 0; i < counts[t]; ++i) {
       Kernel k;
       k.d = &tabs[t][i];
+      k.func = k.d->func;
+      for (int u = 3; u < 6 && !k.func; ++u)  // the direct catalogues
+        for (int j = 0; j < counts[u] && !k.func; ++j) {
+          const KernelDesc& e = tabs[u][j];
+          if (e.dtype == k.d->dtype && e.ta == k.d->ta && e.tb == k.d->tb && e.bm == k.d->bm && e.bn == k.d->bn)
+            k.func = e.func;
+        }
+      if (!k.func) return fail(ctx, GDY_ERR_UNSUPPORTED, "no kernel for %s", k.d->name);
       if (host_only) {
         k.occupancy = host_occupancy(k.d);
         k.vgprs = 0;
       } else {
         int occ = 0;
-        HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k.d->func, k.d->waves * 64, 0));
+        HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k.func, k.d->waves * 64, 0));
         hipFuncAttributes attr;
-        HIP_TRY(ctx, hipFuncGetAttributes(&attr, k.d->func));
+        HIP_TRY(ctx, hipFuncGetAttributes(&attr, k.func));
         k.occupancy = occ;
         k.vgprs = attr.numRegs;
       }
       const int kid = (int)ctx->kernels.size();
       k.code = kid;
       for (int e = kid; e-- > 0;)
-        if (ctx->kernels[e].d->func == k.d->func) k.code = e;
+        if (ctx->kernels[e].func == k.func) k.code = e;
       ctx->kernels.push_back(k);
       for (int c = 0; c < kNumCaps; ++c) {
         if (k.d->ew && kCaps[c] != 0) continue;  // the element-wise add has no grid caps
@@ -1939,22 +2104,35 @@ gdy_status gdy_dispatch_map(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int3
   if (s != GDY_OK) return s;
   if (dispatch < 0 || dispatch >= p.n_dispatches) return fail(ctx, GDY_ERR_INVALID_ARG, "no dispatch %d", dispatch);
   try {
-    const std::vector<int> members = dispatch_members(p, dispatch);
+    // the launch that holds the dispatch; workgroups of its other dispatches
+    // count as idle
+    std::vector<int> members = dispatch_members(p, dispatch);
+    std::vector<int> ids;
+    std::vector<std::vector<int>> of;
+    group_dispatches(p, p.group_of[members[0]], &ids, &of);
+    int joint = 0;
+    for (const Unit& x : launch_units(ctx, gemms, p, mode, ids, of))
+      if (std::find(x.ids.begin(), x.ids.end(), dispatch) != x.ids.end()) {
+        members = x.members;
+        joint = x.joint;
+      }
     const std::vector<int64_t> ws_off = ws_offsets(gemms, p, mode);
     KLaunch L;
     int g = 0;
     bool split = false;
     // the planes' base is never dereferenced here
-    s = build_launch(ctx, gemms, p, members, ws_off, reinterpret_cast<float*>(256), kSplitWsBytes, &L, &g, &split);
+    s = build_launch(ctx, gemms, p, members, joint, ws_off, reinterpret_cast<float*>(256), kSplitWsBytes, &L, &g, &split);
     if (s != GDY_OK) return s;
     *grid = g;
     for (int i = 0; i < n; ++i) items_of_gemm[i] = 0;
     for (int u = 0; u < L.count; ++u)
-      items_of_gemm[members[u]] = (int64_t)L.g[u].tiles_m * L.g[u].tiles_n * std::max(L.g[u].batch, 1) *
+      if (p.dispatch_of[members[u]] == dispatch)
+        items_of_gemm[members[u]] = (int64_t)L.g[u].tiles_m * L.g[u].tiles_n * std::max(L.g[u].batch, 1) *
                                   std::max(L.g[u].split, 1);
     for (int b = 0; b < std::min(g, max_workgroups); ++b) {
       int gi = -1, lwg = 0, nwg = 0;
       locate(L, b, gi, lwg, nwg);
+      if (gi >= 0 && p.dispatch_of[members[gi]] != dispatch) gi = -1;
       gemm_of_wg[b] = gi < 0 ? -1 : members[gi];
       first_item[b] = gi < 0 ? 0 : lwg;
       item_stride[b] = gi < 0 ? 0 : nwg;

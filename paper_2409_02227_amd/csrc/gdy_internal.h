@@ -33,6 +33,7 @@ struct KArgs {
   int32_t group_m;    // tile-order swizzle: tile rows per group
   int32_t xcd_remap;  // 1: keep consecutive tiles on one XCD
   int32_t batch;      // items of a strided batch (>= 1); the extents above are per item
+  int32_t code;       // joint launches: the member's tile and layout
   int32_t ew;         // 0: a GEMM; else the DT_* of an element-wise add (C = A + B)
   int32_t split;      // split-K: K tiles are cut into `split` runs of `split_kt` tiles;
   int32_t split_kt;   //   each run writes an fp32 M x N plane, a reduction kernel sums them
@@ -115,10 +116,15 @@ struct KernelDesc {
   int waves;          // waves per workgroup
   int mfma;           // 32 -> 32x32 MFMA blocks, 16 -> 16x16 blocks
   int lds_bytes;      // static LDS per workgroup
-  const void* func;   // __global__ entry, launched with hipExtLaunchKernel
+  const void* func;   // __global__ entry, launched with hipExtLaunchKernel (null: that of the
+                      // direct kernel with this type, layout and tile)
   int direct;         // 1: global->LDS copies; needs K % bk == 0 and 16-byte alignment
   int ew;             // 1: the element-wise add (a non-GEMM op), not a GEMM kernel
   const void* func_split;  // GEMM kernels: the split-K twin (runs split = 1 GEMMs too)
+  int joint;          // family whose joint kernel can run this kernel's GEMMs: 1 (256 threads),
+                      // 2 (512 threads), 0 none
+  int joint_code;     // KArgs::code there, and the tile it runs
+  int joint_bm, joint_bn;
 };
 
 // Each instantiation unit exports its table.
@@ -129,6 +135,10 @@ int kernels_f32(const KernelDesc** out);
 int kernels_ew(const KernelDesc** out);
 // Split-K reduction kernel for an output type (DT_BF16, DT_F16, DT_F32).
 const void* split_reduce_kernel(int out_dt);
+// Joint kernel of a family (1, 2) for an input type; null if it has none.
+const void* joint_bf16(int family);
+const void* joint_f16(int family);
+const void* joint_fp8(int family);
 int kernels_d_bf16(const KernelDesc** out);
 int kernels_d_f16(const KernelDesc** out);
 int kernels_d_fp8(const KernelDesc** out);

@@ -64,7 +64,7 @@ template <int DT> struct PCfg {
 };
 
 // One operand's copies into half tiles; KC: K-contiguous, else k-major.
-template <int ES, bool KC> struct PhaseCopy {
+template <int ES, bool KC, bool SPILLS> struct PhaseCopy {
   int off[2][2];  // per-lane byte offsets of the wave's two copies of each half
   int kbyte;      // KC: first K byte of this lane's chunk within the tile
   int step;       // bytes from one K tile to the next
@@ -100,32 +100,24 @@ template <int ES, bool KC> struct PhaseCopy {
     for (int j = 0; j < 2; ++j) {
       int o = off[hf][j];
       if constexpr (KC) o = kbyte < kbytes - kt * 128 ? o : kOutOfRange;
-      copy16_to_lds(d, dst + (wave + 8 * j) * 1024, o);
+      copy16_to_lds<SPILLS>(d, dst + (wave + 8 * j) * 1024, o);
     }
   }
 };
 
-template <int DT, int TA, int TB>
-__global__ void __launch_bounds__(512)
-go_gemm_p(KLaunch L) {
+// The tiles of one member (work items lwg, lwg + nwg, ... of p), in the kPLds
+// bytes at smem.
+template <int DT, int TA, int TB, bool JOINT>
+__device__ __forceinline__ void p_tiles(const KArgs& args, int lwg, int nwg, lds_u8* smem) {
+  const Args<JOINT> own(args);
+  const KArgs& p = own.v;
+  if constexpr (JOINT) lwg = uniform(lwg), nwg = uniform(nwg);
   typedef PCfg<DT> C;
   typedef Mma<DT, 16> M;
   typedef typename FragT<C::ES>::T Frag;
   typedef typename M::Acc Acc;
   typedef TileT<C::ES, 128> PT;  // a k-major half tile
   constexpr int NHH = PT::NHH;
-
-  __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[kPLds];
-  lds_u8* smem = (lds_u8*)smem_raw;
-
-  int gi, lwg, nwg;
-  locate(L, gi, lwg, nwg);
-  if (gi < 0) return;  // an idle slot of a placed dispatch
-  const KArgs& p = L.g[gi];
-  if (p.ew) {  // an element-wise add fused into this dispatch
-    ew_member<512>(p, lwg, nwg);
-    return;
-  }
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -165,8 +157,8 @@ go_gemm_p(KLaunch L) {
     const int m0 = tm * 256, n0 = tn * 256;
     const bool half = Mrows - m0 <= 128;  // a 128-row tile
 
-    PhaseCopy<C::ES, TA == 0> ca;
-    PhaseCopy<C::ES, TB == 1> cb;
+    PhaseCopy<C::ES, TA == 0, JOINT> ca;
+    PhaseCopy<C::ES, TB == 1, JOINT> cb;
     ca.init(lda_b, m0, wave, lane);
     cb.init(ldb_b, n0, wave, lane);
 
@@ -311,6 +303,41 @@ go_gemm_p(KLaunch L) {
   }
 }
 
+template <int DT, int TA, int TB>
+__global__ void __launch_bounds__(512)
+go_gemm_p(KLaunch L) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kPLds];
+  int gi, lwg, nwg;
+  locate(L, gi, lwg, nwg);
+  if (gi < 0) return;  // an idle slot of a placed dispatch
+  const KArgs& p = L.g[gi];
+  if (p.ew) ew_member<512>(p, lwg, nwg);  // an element-wise add fused into this dispatch
+  else p_tiles<DT, TA, TB, false>(p, lwg, nwg, (lds_u8*)smem);
+}
+
+// Joint launch of 256 x 256 members of different layouts (KArgs::code =
+// 2*TA + TB): one grid instead of a dispatch, fork and join per layout.
+template <int DT>
+__global__ void __launch_bounds__(512)
+go_gemm_p_joint(KLaunch L) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[kPLds];
+  lds_u8* smem = (lds_u8*)smem_raw;
+  int gi, lwg, nwg;
+  locate(L, gi, lwg, nwg);
+  if (gi < 0) return;
+  const KArgs& p = L.g[gi];
+  if (p.ew) {
+    ew_member<512>(p, lwg, nwg);
+    return;
+  }
+  switch (p.code) {
+    case 0: p_tiles<DT, 0, 0, true>(p, lwg, nwg, smem); break;
+    case 1: p_tiles<DT, 0, 1, true>(p, lwg, nwg, smem); break;
+    case 2: p_tiles<DT, 1, 0, true>(p, lwg, nwg, smem); break;
+    default: p_tiles<DT, 1, 1, true>(p, lwg, nwg, smem);
+  }
+}
+
 }  // namespace gdy
 
 // Catalogue entries.  One kernel serves every 256 x 256 name of the direct
@@ -321,4 +348,5 @@ go_gemm_p(KLaunch L) {
 // limit, so it has no split twin.
 #define GDY_KERNEL_P(DT, DTNAME, TA, TB, LAYOUT, SUFFIX, KB)                                     \
   {DTNAME "_" LAYOUT "_256x256_" SUFFIX, DT, TA, TB, 256, 256, KB / ::gdy::ElemSize<DT>::v, 8, 16, \
-   ::gdy::kPLds, reinterpret_cast<const void*>(&::gdy::go_gemm_p<DT, TA, TB>), 1, 0, nullptr}
+   ::gdy::kPLds, reinterpret_cast<const void*>(&::gdy::go_gemm_p<DT, TA, TB>), 1, 0, nullptr,                     \
+   2, 2 * TA + TB, 256, 256}

@@ -34,7 +34,7 @@ namespace gdy {
 // One operand of a tile: ROWS rows (or columns) x 128 bytes of K, KC:
 // K-contiguous.  Lane `lane` of wave `wave` owns the chunks at LDS bytes
 // (wave + NW*j)*1024 + lane*16 in both ways.
-template <int ES, bool KC, int ROWS, int NW> struct Operand {
+template <int ES, bool KC, int ROWS, int NW, bool SPILLS> struct Operand {
   static constexpr int BLOCKS = ROWS / 8;                   // 1 KiB copies of a K tile
   static constexpr int N = BLOCKS < NW ? 1 : BLOCKS / NW;   // chunks per lane
   static constexpr bool ALL = BLOCKS >= NW;                 // every wave takes part (16-row tiles: two do)
@@ -82,7 +82,7 @@ template <int ES, bool KC, int ROWS, int NW> struct Operand {
     for (int j = 0; j < N; ++j) {
       int o = at(j);
       if constexpr (KC) o = kpos[0] < kbytes - kt * 128 ? o : kOutOfRange;
-      copy16_to_lds(d, dst + (wave + NW * j) * 1024, o);
+      copy16_to_lds<SPILLS>(d, dst + (wave + NW * j) * 1024, o);
     }
   }
   __device__ __forceinline__ void load(int kt, int wave) {
@@ -136,30 +136,22 @@ template <int DT, int BM, int BN, int WM, int WN, int STAGES> struct UCfg {
   static_assert(LDS <= 160 * 1024, "LDS budget");
 };
 
-template <int DT, int TA, int TB, int BM, int BN, int WM, int WN, int STAGES, bool ANY, bool SPLIT>
-__global__ void __launch_bounds__(WM * WN * 64)
-go_gemm_u(KLaunch L) {
-  static_assert(!ANY || STAGES == 2, "the register way is a tile ahead of two stages");
+// The tiles of one member: work items lwg, lwg + nwg, ... of p, by the whole
+// workgroup, in the LDS at smem (UCfg::LDS bytes).  ANY: both ways, else
+// copies only.  SPLIT: members may be split along K.
+template <int DT, int TA, int TB, int BM, int BN, int WM, int WN, int STAGES, bool ANY, bool SPLIT, bool JOINT>
+__device__ __forceinline__ void u_tiles(const KArgs& args, int lwg, int nwg, lds_u8* smem) {
+  const Args<JOINT> own(args);
+  const KArgs& p = own.v;
+  if constexpr (JOINT) lwg = uniform(lwg), nwg = uniform(nwg);
   typedef UCfg<DT, BM, BN, WM, WN, STAGES> C;
   typedef Mma<DT, 16> M;
   typedef typename FragT<C::ES>::T Frag;
   typedef typename M::Acc Acc;
-  typedef Operand<C::ES, TA == 0, BM, C::NW> OpA;
-  typedef Operand<C::ES, TB == 1, BN, C::NW> OpB;
+  typedef Operand<C::ES, TA == 0, BM, C::NW, ANY || JOINT> OpA;
+  typedef Operand<C::ES, TB == 1, BN, C::NW, ANY || JOINT> OpB;
   constexpr int NHH = OpA::T::NHH;
   constexpr int WTM = BM / WM, WTN = BN / WN;
-
-  __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[C::LDS];
-  lds_u8* smem = (lds_u8*)smem_raw;
-
-  int gi, lwg, nwg;
-  locate(L, gi, lwg, nwg);
-  if (gi < 0) return;  // an idle slot of a placed dispatch
-  const KArgs& p = L.g[gi];
-  if (p.ew) {  // an element-wise add fused into this dispatch
-    ew_member<C::NW * 64>(p, lwg, nwg);
-    return;
-  }
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -263,7 +255,7 @@ go_gemm_u(KLaunch L) {
     };
 
     if (nk > 0) {
-      if constexpr (ANY) {
+      if (ANY && (STAGES == 2 || !acopy || !bcopy)) {
         // tile kt to its stage (register way: the values loaded before), and
         // the loads of the tile after it
         auto stage_in = [&](int kt) {
@@ -294,7 +286,7 @@ go_gemm_u(KLaunch L) {
       } else {
         // ring: STAGES - 1 tiles in flight while one is computed
         constexpr int PER = OpA::N + OpB::N;  // copies of a wave per tile
-        static_assert(OpA::ALL && OpB::ALL && (STAGES - 2) * PER < 64, "counted copies");
+        static_assert((ANY && STAGES == 2) || (OpA::ALL && OpB::ALL && (STAGES - 2) * PER < 64), "counted copies");
         wait_vmcnt<0>();  // the previous tile's stores
 #pragma unroll
         for (int s = 0; s < STAGES - 1; ++s)
@@ -358,6 +350,73 @@ go_gemm_u(KLaunch L) {
   }
 }
 
+template <int DT, int TA, int TB, int BM, int BN, int WM, int WN, int STAGES, bool ANY, bool SPLIT>
+__global__ void __launch_bounds__(WM * WN * 64)
+go_gemm_u(KLaunch L) {
+  static_assert(!ANY || STAGES == 2, "the register way is a tile ahead of two stages");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[UCfg<DT, BM, BN, WM, WN, STAGES>::LDS];
+  int gi, lwg, nwg;
+  locate(L, gi, lwg, nwg);
+  if (gi < 0) return;  // an idle slot of a placed dispatch
+  const KArgs& p = L.g[gi];
+  if (p.ew) ew_member<WM * WN * 64>(p, lwg, nwg);  // an element-wise add fused into this dispatch
+  else u_tiles<DT, TA, TB, BM, BN, WM, WN, STAGES, ANY, SPLIT, false>(p, lwg, nwg, (lds_u8*)smem);
+}
+
+// ---------------------------------------------------------------------------
+// Joint launches.  A group whose GEMMs bind several kernels of one type (tiles,
+// layouts, alignments) would take a dispatch each, and a fork and join of a
+// pool stream per dispatch cost 20-25 us, more than a short group's GEMMs.
+// This kernel runs them in one grid: each member names its tile and layout
+// (KArgs::code), and runs the same loop as in its own kernel.  A tile size
+// changes where an element is computed, never its sum (one MFMA shape, K
+// ascending), so results are those of the members' own kernels bit for bit.
+// Registers and LDS are those of the largest member: two workgroups a CU.
+// ---------------------------------------------------------------------------
+// Codes: layout (2*TA + TB) * 8 + tile.  Tiles above 128 x 128 run as 128 x 128,
+// wide ones as the 128-column (64 for 16 rows) tile of their height.
+constexpr int joint_tile(int bm, int bn) {
+  return bm >= 128 ? 0 : bm == 64 ? (bn == 64 ? 2 : 1) : bm == 32 ? 3 : 4;
+}
+constexpr int kJointBm[5] = {128, 64, 64, 32, 16}, kJointBn[5] = {128, 128, 64, 128, 64};
+constexpr int joint_code(int ta, int tb, int bm, int bn) { return (2 * ta + tb) * 8 + joint_tile(bm, bn); }
+constexpr int kJointLds = 80 * 1024;
+
+template <int DT, int TA, int TB>
+__device__ __forceinline__ void joint_tiles(const KArgs& p, int lwg, int nwg, lds_u8* smem) {
+  switch (p.code & 7) {
+    case 0: u_tiles<DT, TA, TB, 128, 128, 2, 2, 2, true, true, true>(p, lwg, nwg, smem); break;
+    case 2: u_tiles<DT, TA, TB, 64, 64, 2, 2, 4, true, true, true>(p, lwg, nwg, smem); break;
+    case 4: u_tiles<DT, TA, TB, 16, 64, 1, 4, 2, true, true, true>(p, lwg, nwg, smem); break;
+    default:  // the catalogue has these for an untransposed A only
+      if constexpr (TA == 0) {
+        if ((p.code & 7) == 1) u_tiles<DT, TA, TB, 64, 128, 2, 2, 3, true, true, true>(p, lwg, nwg, smem);
+        else u_tiles<DT, TA, TB, 32, 128, 1, 4, 4, true, true, true>(p, lwg, nwg, smem);
+      }
+  }
+}
+
+template <int DT>
+__global__ void __launch_bounds__(256)
+go_gemm_joint(KLaunch L) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[kJointLds];
+  lds_u8* smem = (lds_u8*)smem_raw;
+  int gi, lwg, nwg;
+  locate(L, gi, lwg, nwg);
+  if (gi < 0) return;
+  const KArgs& p = L.g[gi];
+  if (p.ew) {
+    ew_member<256>(p, lwg, nwg);
+    return;
+  }
+  switch (p.code >> 3) {
+    case 0: joint_tiles<DT, 0, 0>(p, lwg, nwg, smem); break;
+    case 1: joint_tiles<DT, 0, 1>(p, lwg, nwg, smem); break;
+    case 2: joint_tiles<DT, 1, 0>(p, lwg, nwg, smem); break;
+    default: joint_tiles<DT, 1, 1>(p, lwg, nwg, smem);
+  }
+}
+
 }  // namespace gdy
 
 // Catalogue entries.  _m32 / _m16: any operands (the names are those of the
@@ -367,7 +426,9 @@ go_gemm_u(KLaunch L) {
   {NAME, DT, TA, TB, BM, BN, ::gdy::UCfg<DT, BM, BN, WM, WN, ST>::BK, WM * WN, 16,                   \
    ::gdy::UCfg<DT, BM, BN, WM, WN, ST>::LDS,                                                          \
    reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, ST, ANY, false>), DIRECT, 0, \
-   reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, ST, ANY, true>)}
+   reinterpret_cast<const void*>(&::gdy::go_gemm_u<DT, TA, TB, BM, BN, WM, WN, ST, ANY, true>),       \
+   WM * WN == 4 ? 1 : 0, ::gdy::joint_code(TA, TB, BM, BN),                                           \
+   ::gdy::kJointBm[::gdy::joint_tile(BM, BN)], ::gdy::kJointBn[::gdy::joint_tile(BM, BN)]}
 #define GDY_KERNEL_U(DT, DTNAME, TA, TB, LAYOUT, BM, BN, WM, WN, MM)                                  \
   GDY_KERNEL_UX(DT, TA, TB, BM, BN, WM, WN, 2, true, 0,                                               \
                 DTNAME "_" LAYOUT "_" #BM "x" #BN "_w" #WM "x" #WN "_m" #MM)

@@ -13,6 +13,7 @@
   GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 128, 128, 2, 2, 4)
 
 #define GDY_TILES_D_SMALL(L, TA, TB)                                  \
+  GDY_KERNEL_P(GDY_DT, GDY_DTNAME, TA, TB, L, "w2x4_d2", 128),        \
   GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 256, 128, 2, 2, 3),     \
   GDY_KERNEL_D(GDY_DT, GDY_DTNAME, TA, TB, L, 128, 128, 2, 2, 2)
 

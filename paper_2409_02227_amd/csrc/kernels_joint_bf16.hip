@@ -1,0 +1,7 @@
+// Joint launches of bf16 GEMMs that bind different kernels.
+#include "go_kernel_u.h"
+const void* gdy::joint_bf16(int family) {
+  return family == 1   ? reinterpret_cast<const void*>(&go_gemm_joint<DT_BF16>)
+         : family == 2 ? reinterpret_cast<const void*>(&go_gemm_p_joint<DT_BF16>)
+                       : nullptr;
+}

@@ -53,16 +53,58 @@ __device__ __forceinline__ sdesc make_sdesc(const void* base, int bytes) {
 constexpr int kOutOfRange = 0x7ffffff0;  // past any operand's extent: the copy writes zeros
 
 // One 16-byte copy per lane: global byte `voffset` of `d` -> LDS address
-// lds_addr + 16 * lane (lds_addr is wave-uniform).  The s_nop is the wait
-// state a copy to LDS needs after the write of M0 (the compiler inserts none
-// in front of inline assembly).
+// lds_addr + 16 * lane (lds_addr is wave-uniform).  The s_nop gives the wait
+// states that the compiler does not insert in front of inline assembly: one
+// after the write of M0 and, with SPILLS, five after a vector instruction that
+// wrote a register of the descriptor.  Only kernels that keep scalars in lanes
+// of vector registers (the build's resource report counts them as spilled
+// SGPRs) have such writes; the five cost 2% of an 8192^3 GEMM.
+template <bool SPILLS>
 __device__ __forceinline__ void copy16_to_lds(sdesc d, const lds_u8* lds_base, int voffset) {
   const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds_base);
-  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
-               : "{m0}"(lds_addr), "v"(voffset), "s"(d)
-               : "memory");
+  if constexpr (SPILLS)
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "{m0}"(lds_addr), "v"(voffset), "s"(d)
+                 : "memory");
+  else
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "{m0}"(lds_addr), "v"(voffset), "s"(d)
+                 : "memory");
 }
+
+// A workgroup-uniform value in scalar registers (nothing where the compiler
+// knows; in the joint kernels, too large for it to follow the argument block's
+// loads, it would keep the copies' descriptors in vector registers).
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  return (int64_t)(((uint64_t)(uint32_t)uniform((int)(x >> 32)) << 32) | (uint32_t)uniform((int)x));
+}
+template <class T> __device__ __forceinline__ T* uniform(T* p) { return (T*)uniform((int64_t)p); }
+// The members of an argument block that the tile loops use, as scalars.
+__device__ __forceinline__ KArgs uniform(const KArgs& q) {
+  KArgs p = q;
+  p.a = uniform(q.a), p.b = uniform(q.b), p.c = uniform(q.c);
+  p.m = uniform((int)q.m), p.n = uniform((int)q.n), p.k = uniform((int)q.k);
+  p.lda = uniform((int)q.lda), p.ldb = uniform((int)q.ldb), p.ldc = uniform((int)q.ldc);
+  p.a_bytes = uniform(q.a_bytes), p.b_bytes = uniform(q.b_bytes), p.c_bytes = uniform(q.c_bytes);
+  p.tiles_m = uniform(q.tiles_m), p.tiles_n = uniform(q.tiles_n), p.batch = uniform(q.batch);
+  p.c_vec = uniform(q.c_vec), p.a_dma = uniform(q.a_dma), p.b_dma = uniform(q.b_dma);
+  p.split = uniform(q.split), p.split_kt = uniform(q.split_kt), p.ws = uniform(q.ws);
+  p.stride_a = uniform(q.stride_a), p.stride_b = uniform(q.stride_b), p.stride_c = uniform(q.stride_c);
+  return p;
+}
+
+// A member's arguments in its own kernel (as they are) and in a joint one.
+template <bool JOINT> struct Args {
+  const KArgs& v;
+  __device__ __forceinline__ Args(const KArgs& a) : v(a) {}
+};
+template <> struct Args<true> {
+  KArgs v;
+  __device__ __forceinline__ Args(const KArgs& a) : v(uniform(a)) {}
+};
 
 // Workgroup barrier the compiler does not decorate with memory waits; the
 // caller has already waited for its own copies.

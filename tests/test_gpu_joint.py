@@ -1,0 +1,103 @@
+"""Joint launches (csrc/go_kernel_u.h go_gemm_joint, go_kernel_p.h
+go_gemm_p_joint): a group whose GEMMs bind several kernels of one type runs
+them in one grid.  Each GEMM's result equals, bit for bit, its run alone on
+the kernel the plan names, over layouts, tiles, alignments, split K and adds;
+and the oracle's."""
+import numpy as np
+import pytest
+
+import paper_2409_02227_amd  # noqa: F401  (sets GPU_MAX_HW_QUEUES before HIP starts)
+
+torch = pytest.importorskip("torch")
+
+from paper_2409_02227_amd import gdy, inputs  # noqa: E402
+from paper_2409_02227_amd.inputs import GemmSpec  # noqa: E402
+from tests.gpu_helpers import check, check_add, gemm_of, out_codes, reset_outputs  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    c = gdy.Context(0)  # no table: GO binds every GEMM to its isolated heuristic
+    yield c
+    c.close()
+
+
+SHAPES = [("nn", 300, 1000, 520, 0), ("nt", 77, 512, 1024, 0), ("nt", 1000, 640, 512, 1), ("nn", 16, 1024, 4096, 0),
+          ("tn", 256, 300, 200, 0), ("tt", 130, 128, 384, 8), ("nn", 1, 700, 333, 3), ("nt", 33, 257, 2048, 0),
+          ("tn", 513, 515, 1040, 1), ("nn", 260, 260, 64, 0)]
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16", "fp8"])
+@pytest.mark.parametrize("count", [2, 5, 10])
+def test_bits_and_values(ctx, dt, count):
+    mats = [inputs.materialize(GemmSpec(m, n, k, dt, int(lay[0] == "t"), int(lay[1] == "t"), seed=9500 + i, pad_a=pad,
+                                        pad_b=pad, name=f"{dt}_{lay}_{m}x{n}x{k}"))
+            for i, (lay, m, n, k, pad) in enumerate(SHAPES[:count])]
+    # kernels of every tile and both families, named one by one
+    names = ["128x128_w2x2_m32", "64x64_w2x2_m32", "256x256_w2x4_m32", "16x64_w1x4_m16"]
+    for rnd in range(len(names)):
+        vids = [ctx.find(f"{dt}_{SHAPES[i][0]}_{names[(i + rnd) % len(names)]}_c0") for i in range(count)]
+        assert min(vids) >= 0
+        alone = []
+        for m, v in zip(mats, vids):
+            reset_outputs([m])
+            ctx.execute([gemm_of(m, v)], mode="forced")
+            torch.cuda.synchronize()
+            check(m, label="alone")
+            alone.append(out_codes(m).copy())
+        reset_outputs(mats)
+        ctx.execute([gemm_of(m, v) for m, v in zip(mats, vids)], mode="forced_grouped")
+        torch.cuda.synchronize()
+        for m, ref in zip(mats, alone):
+            assert np.array_equal(out_codes(m), ref), m.spec.name
+    reset_outputs(mats)
+    plan = ctx.execute([gemm_of(m) for m in mats], mode="go", want_plan=True)
+    torch.cuda.synchronize()
+    got = [out_codes(m).copy() for m in mats]
+    for m, v, bits in zip(mats, plan["variant_of"], got):
+        check(m, label="go")
+        reset_outputs([m])
+        ctx.execute([gemm_of(m, v)], mode="forced")
+        torch.cuda.synchronize()
+        assert np.array_equal(out_codes(m), bits), (m.spec.name, ctx.variant(v)["name"])
+
+
+def test_table_bound_kernels_join(ctx, tmp_path):
+    """GO under a table that binds each GEMM to a kernel of another tile and
+    layout: one stream, and the bits of each kernel run alone; an add rides
+    along."""
+    rows = [("nn", 300, 1024, 512, "64x64_w2x2_d4"), ("nt", 77, 512, 1024, "128x128_w2x2_d2"),
+            ("nt", 1000, 640, 512, "256x256_w2x4_d2"), ("nn", 16, 1024, 4096, "32x128_w1x4_d4"),
+            ("tn", 256, 304, 256, "256x256_w2x4_d2"), ("nn", 40, 2048, 2048, "64x256_w1x4_d3"),
+            ("nn", 512, 512, 192, "256x128_w2x2_d3"), ("tt", 128, 128, 384, "64x64_w2x2_d4")]
+    lines = ["gdy-go-table 2", f"device gfx950 cus {ctx.cus()}", f"catalogue {ctx.catalogue_hash():016x}"]
+    mats = []
+    for i, (lay, m, n, k, name) in enumerate(rows):
+        ta, tb = int(lay[0] == "t"), int(lay[1] == "t")
+        lines.append(f"entry 2 {ta} {tb} {(m - 1).bit_length()} {n} {k} 1 " + " ".join([f"bf16_{lay}_{name}_c0"] * 5))
+        mats.append(inputs.materialize(GemmSpec(m, n, k, "bf16", ta, tb, seed=9600 + i, name=f"{lay}_{m}x{n}x{k}")))
+    path = tmp_path / "joint.table"
+    path.write_text("\n".join(lines) + "\n")
+    t = gdy.Context(0, table=str(path))
+    try:
+        add = inputs.materialize_add(200, 1000, "bf16", seed=4)
+        reset_outputs(mats)
+        add.c_full.fill_(float("nan"))
+        plan = t.execute([gemm_of(m) for m in mats] + [gdy.Add(add.a, add.b, add.c)], mode="go", want_plan=True)
+        torch.cuda.synchronize()
+        assert [t.variant(v)["name"] for v in plan["variant_of"][:8]] == [f"bf16_{r[0]}_{r[4]}_c0" for r in rows]
+        assert plan["fallback"] == 0 and set(plan["stream_of"]) == {-1}  # a short group: one launch
+        check_add(add)
+        got = [out_codes(m).copy() for m in mats]
+        for m, v, bits in zip(mats, plan["variant_of"], got):
+            check(m, label="joint")
+            reset_outputs([m])
+            t.execute([gemm_of(m, v)], mode="forced")
+            torch.cuda.synchronize()
+            assert np.array_equal(out_codes(m), bits), m.spec.name
+    finally:
+        t.close()
