@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgdy.so")
 
-SOURCES = ["kernels_joint_bf16.hip", "kernels_joint_f16.hip", "kernels_joint_fp8.hip",
+SOURCES = ["kernels_joint_bf16.hip", "kernels_joint_f16.hip", "kernels_joint_fp8.hip", "kernels_joint_f32.hip",
            "kernels_d_bf16.hip", "kernels_d_f16.hip", "kernels_d_fp8.hip",
            "kernels_bf16.hip", "kernels_f16.hip", "kernels_fp8.hip", "kernels_f32.hip", "kernels_ew.hip", "gdy.cpp"]
 ARCH = "gfx950"

@@ -681,13 +681,15 @@ bool b_copies(const gdy_gemm& g) {
 
 const void* joint_kernel(int dtype, int family) {
   return dtype == DT_BF16 ? joint_bf16(family) : dtype == DT_F16 ? joint_f16(family)
-         : dtype == DT_FP8 ? joint_fp8(family) : nullptr;
+         : dtype == DT_FP8 ? joint_fp8(family) : dtype == DT_F32 ? joint_f32(family) : nullptr;
 }
 
 // How a GEMM (or add) runs on a variant: its kernel, and the family, member
-// code and tile of a joint launch (family 0: none takes it).  The 256 x 256
-// kernel for any operands is the alternating one where both take copies; other
-// GEMMs run as 128 x 128 tiles of the joint kernel, alone too.
+// code and tile of a joint launch (family 0: none takes it).  Catalogue entries
+// without a function of their own (kernels_list.h says why): fp32 tiles above
+// 128 x 128 run as 128 x 128 ones; the 256 x 256 kernel for any operands is the
+// alternating one where both take copies, else 128 x 128 tiles of the joint
+// kernel, alone too.
 struct Exec {
   const void *func, *func_split;
   int waves, bm, bn;        // of its own launch
@@ -699,7 +701,11 @@ Exec exec_of(const gdy_ctx* ctx, int vid, const gdy_gemm& g) {
   const Kernel& k = ctx->kernels[ctx->variants[vid].kernel];
   const KernelDesc* d = k.d;
   Exec e = {k.func, d->func_split, d->waves, d->bm, d->bn, d->joint, d->joint_code, d->joint_bm, d->joint_bn, 2 * k.code};
-  if (d->joint == 2 && !d->direct && !(a_copies(g) && b_copies(g))) {
+  if (!d->func && d->dtype == DT_F32) {
+    e.waves = 4;
+    e.bm = e.bn = 128;
+    e.key = 2 * ctx->variants[vid].kernel + 1;
+  } else if (!d->func && !(a_copies(g) && b_copies(g))) {
     e.func = e.func_split = joint_kernel(d->dtype, 1);
     e.waves = 4;
     e.bm = e.bn = e.jbm = e.jbn = 128;
@@ -1856,10 +1862,13 @@ static gdy_status create_impl(gdy_ctx* ctx, int device, const char* table_path, 
       Kernel k;
       k.d = &tabs[t][i];
       k.func = k.d->func;
-      for (int u = 3; u < 6 && !k.func; ++u)  // the direct catalogues
+      // a kernel that another one runs: fp32 tiles above 128 x 128 that one, 256
+      // x 256 for any operands the direct 256 x 256
+      const int large = k.d->dtype == DT_F32 ? 128 : 256;
+      for (int u = 0; u < kTables && !k.func; ++u)
         for (int j = 0; j < counts[u] && !k.func; ++j) {
           const KernelDesc& e = tabs[u][j];
-          if (e.dtype == k.d->dtype && e.ta == k.d->ta && e.tb == k.d->tb && e.bm == k.d->bm && e.bn == k.d->bn)
+          if (e.dtype == k.d->dtype && e.ta == k.d->ta && e.tb == k.d->tb && e.bm == large && e.bn == large && !e.ew)
             k.func = e.func;
         }
       if (!k.func) return fail(ctx, GDY_ERR_UNSUPPORTED, "no kernel for %s", k.d->name);
@@ -1871,7 +1880,7 @@ static gdy_status create_impl(gdy_ctx* ctx, int device, const char* table_path, 
         HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k.func, k.d->waves * 64, 0));
         hipFuncAttributes attr;
         HIP_TRY(ctx, hipFuncGetAttributes(&attr, k.func));
-        k.occupancy = occ;
+        k.occupancy = k.d->func ? occ : host_occupancy(k.d);  // of the tile it is named for
         k.vgprs = attr.numRegs;
       }
       const int kid = (int)ctx->kernels.size();

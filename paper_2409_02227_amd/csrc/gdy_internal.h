@@ -116,8 +116,8 @@ struct KernelDesc {
   int waves;          // waves per workgroup
   int mfma;           // 32 -> 32x32 MFMA blocks, 16 -> 16x16 blocks
   int lds_bytes;      // static LDS per workgroup
-  const void* func;   // __global__ entry, launched with hipExtLaunchKernel (null: that of the
-                      // direct kernel with this type, layout and tile)
+  const void* func;   // __global__ entry, launched with hipExtLaunchKernel (null: another
+                      // catalogue kernel runs its GEMMs, see exec_of)
   int direct;         // 1: global->LDS copies; needs K % bk == 0 and 16-byte alignment
   int ew;             // 1: the element-wise add (a non-GEMM op), not a GEMM kernel
   const void* func_split;  // GEMM kernels: the split-K twin (runs split = 1 GEMMs too)
@@ -139,6 +139,7 @@ const void* split_reduce_kernel(int out_dt);
 const void* joint_bf16(int family);
 const void* joint_f16(int family);
 const void* joint_fp8(int family);
+const void* joint_f32(int family);
 int kernels_d_bf16(const KernelDesc** out);
 int kernels_d_f16(const KernelDesc** out);
 int kernels_d_fp8(const KernelDesc** out);

@@ -1,5 +1,5 @@
-// go_kernel_u.h -- the GO-Kernels of the 16- and 8-bit types for tiles below
-// 256 x 256, and for operands of any size and alignment.
+// go_kernel_u.h -- the GO-Kernels for tiles below 256 x 256, for operands of any
+// size and alignment, and for fp32.
 //
 // Both operands lie in LDS in the layouts of lds_copy.h, and each gets there by
 // one of two ways, chosen per GEMM:
@@ -131,7 +131,8 @@ template <int DT, int BM, int BN, int WM, int WN, int STAGES> struct UCfg {
   static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128;
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int PITCH = BN * 2 + 16;  // of the rounded tile: a half wave's 16 rows on distinct banks
-  static constexpr int LDS = STAGES * STAGE > BM * PITCH ? STAGES * STAGE : BM * PITCH;
+  static constexpr int OUT = ES == 4 ? 0 : BM * PITCH;  // fp32 results leave from the accumulators
+  static constexpr int LDS = STAGES * STAGE > OUT ? STAGES * STAGE : OUT;
   static_assert(BM % (WM * 16) == 0 && BN % (WN * 16) == 0, "wave tile must hold whole 16 x 16 blocks");
   static_assert(LDS <= 160 * 1024, "LDS budget");
 };
@@ -147,7 +148,7 @@ __device__ __forceinline__ void u_tiles(const KArgs& args, int lwg, int nwg, lds
   typedef UCfg<DT, BM, BN, WM, WN, STAGES> C;
   typedef Mma<DT, 16> M;
   typedef typename FragT<C::ES>::T Frag;
-  typedef typename M::Acc Acc;
+  typedef f32x4 Acc;
   typedef Operand<C::ES, TA == 0, BM, C::NW, ANY || JOINT> OpA;
   typedef Operand<C::ES, TB == 1, BN, C::NW, ANY || JOINT> OpB;
   constexpr int NHH = OpA::T::NHH;
@@ -158,7 +159,7 @@ __device__ __forceinline__ void u_tiles(const KArgs& args, int lwg, int nwg, lds
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int ntiles = p.tiles_m * p.tiles_n;
-  const int lda_b = (int)p.lda * C::ES, ldb_b = (int)p.ldb * C::ES, ldc_b = (int)p.ldc * 2;
+  const int lda_b = (int)p.lda * C::ES, ldb_b = (int)p.ldb * C::ES, ldc_b = (int)p.ldc * OutSize<DT>::v;
   const int Mrows = (int)p.m, Ncols = (int)p.n;
   const bool acopy = !ANY || p.a_dma, bcopy = !ANY || p.b_dma;
   const int a_extent = TA == 0 ? (Mrows - 1) * lda_b + (int)p.k * C::ES : ((int)p.k - 1) * lda_b + Mrows * C::ES;
@@ -234,9 +235,18 @@ __device__ __forceinline__ void u_tiles(const KArgs& args, int lwg, int nwg, lds
         }
         if (ks == 0) between();
 #pragma unroll
-        for (int j = 0; j < C::FN; ++j)
+        for (int s = 0; s < (C::ES == 4 ? 4 : 1); ++s)  // fp32: the four MFMAs of a K step
 #pragma unroll
-          for (int i = 0; i < C::FM; ++i) acc[j][i] = M::run(bf[j], af[i], acc[j][i]);
+          for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+            for (int i = 0; i < C::FM; ++i) {
+              if constexpr (C::ES == 4) {
+                const unsigned b = bf[j][s], a = af[i][s];  // copies: a bit cast of a vector's element takes its first
+                acc[j][i] = M::run(__builtin_bit_cast(float, b), __builtin_bit_cast(float, a), acc[j][i]);
+              } else {
+                acc[j][i] = M::run(bf[j], af[i], acc[j][i]);
+              }
+            }
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -334,6 +344,25 @@ __device__ __forceinline__ void u_tiles(const KArgs& args, int lwg, int nwg, lds
     // accumulator r of lane l is n = 4*(l/16) + r, m = l%16 of its block
     __syncthreads();  // every wave has read its last fragments
     const float s = p.scale;
+    if constexpr (C::ES == 4) {  // 16 bytes a lane, 64 consecutive ones of 16 rows an instruction
+#pragma unroll
+      for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i) {
+          const int row = m0 + wm * WTM + i * 16 + (lane & 15), col = n0 + wn * WTN + j * 16 + 4 * (lane >> 4);
+          if (row >= Mrows) continue;
+          const f32x4 x = acc[j][i] * s;
+          const int off = row * ldc_b + col * 4;
+          if (col + 4 <= Ncols) {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rc, off, 0, 0);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (col + e < Ncols) store_out<DT>(x[e], rc, off + 4 * e);
+          }
+        }
+    }
+    if constexpr (C::ES != 4) {
 #pragma unroll
     for (int j = 0; j < C::FN; ++j)
 #pragma unroll
@@ -346,6 +375,7 @@ __device__ __forceinline__ void u_tiles(const KArgs& args, int lwg, int nwg, lds
     __syncthreads();
     store_tile<BN, C::NW * 64, C::PITCH>(smem, rc, m0 * ldc_b + n0 * 2, ldc_b, min(BM, Mrows - m0),
                                          min(BN, Ncols - n0), p.c_vec != 0, tid);
+    }
     if (tb + nwg < total) __syncthreads();  // the next tile's copies overwrite the output rows
   }
 }

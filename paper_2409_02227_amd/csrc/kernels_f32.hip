@@ -1,6 +1,6 @@
 // GO-Kernel instantiations for fp32 inputs (fp32 MFMA and accumulation,
 // fp32 out): staged tiles only.
-#include "go_kernel.h"
+#include "go_kernel_u.h"
 #define GDY_DT ::gdy::DT_F32
 #define GDY_DTNAME "f32"
 #define GDY_DT32 1

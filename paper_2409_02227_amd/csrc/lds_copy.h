@@ -116,22 +116,25 @@ __device__ __forceinline__ void barrier_nowait() { asm volatile("s_barrier" ::: 
 template <int ES> struct FragT;  // fragment type by element size
 template <> struct FragT<2> { typedef u32x4 T; static constexpr int FB = 16; };
 template <> struct FragT<1> { typedef i32x8 T; static constexpr int FB = 32; };
+// fp32: four K values of a 16 x 16 x 4 MFMA each; MFMA s of a K step takes the
+// s-th value of every lane, K = 16*ks + 4*(l/16) + s for both operands.
+template <> struct FragT<4> { typedef u32x4 T; static constexpr int FB = 16; };
 
 __device__ __forceinline__ u32x4 lds_read16(const lds_u8* p) {
   return *(const __attribute__((address_space(3))) u32x4*)p;
 }
 
 // K-contiguous tile: per-lane offset at K step 0 (8-bit fragments are two
-// chunks, e = 0 and 1); K step ks XORs 64*ks into it (16-bit tiles hold two
-// steps, 8-bit tiles one).
+// chunks, e = 0 and 1); K step ks XORs 64*ks into it (8-bit tiles hold
+// one step, the others two).
 template <int ES> __device__ __forceinline__ int pk_lane(int lane, int e) {
   const int r = lane & 15, g = lane >> 4;
-  const int c = ES == 2 ? g : 2 * g + e;
+  const int c = ES == 1 ? 2 * g + e : g;
   return r * 128 + ((c ^ ((r >> 1) & 7)) << 4);
 }
 template <int ES>
 __device__ __forceinline__ typename FragT<ES>::T pk_frag(const lds_u8* blk, int o0, int o1, int ks) {
-  if constexpr (ES == 2) {
+  if constexpr (ES != 1) {
     return lds_read16(blk + (o0 ^ (64 * ks)));
   } else {
     const u32x4 lo = lds_read16(blk + o0), hi = lds_read16(blk + o1);
@@ -148,14 +151,18 @@ __device__ __forceinline__ typename FragT<ES>::T pk_frag(const lds_u8* blk, int 
 // groups of lanes whose k differ by 8 (32).  Rows of 256 bytes and more all
 // start on bank 0, shorter ones on the bank their k gives; h spreads those that
 // share banks over different chunks (rows of 16 or 32 bytes, the transposed A
-// of 16-row tiles, keep their order: two lanes to a bank).
+// of 16-row tiles, keep their order: two lanes to a bank).  fp32 needs no
+// transpose: a read takes 16 columns of four k-rows 4 apart, one value a lane;
+// their chunks go to different quarters of the banks.
 template <int ES, int ROWS> struct TileT {
   static constexpr int RB = ROWS * ES;
   static constexpr int NCH = RB / 16;
-  static constexpr int NHH = ES == 2 ? 2 : 4;  // transpose reads of a fragment
-  static_assert(RB >= 16 && RB <= 512, "1 to 32 chunks per k-row");
+  static constexpr int NHH = ES == 2 ? 2 : 4;  // reads of a fragment
+  static_assert(RB >= 16 && RB <= 1024, "1 to 64 chunks per k-row");
   static __device__ __forceinline__ int h(int k) {
-    if constexpr (RB < 64) {
+    if constexpr (ES == 4) {
+      return (4 * ((k >> 2) & 3)) & (NCH - 1);
+    } else if constexpr (RB < 64) {
       return 0;
     } else if constexpr (ES == 2) {
       if constexpr (RB >= 256) return (4 * (k & 3)) ^ (2 * ((k >> 3) & 1));
@@ -174,14 +181,19 @@ template <int ES, int ROWS> struct TileT {
   // per-lane offset of sub-read hh of the 16-column fragment at col0, K step 0
   static __device__ __forceinline__ int lane_off(int lane, int col0, int hh) {
     const int L = lane & 15, kb = (lane >> 4) * (FragT<ES>::FB / ES);
-    if constexpr (ES == 2) return addr(kb + 4 * hh + (L >> 2), col0 + 4 * (L & 3));
+    if constexpr (ES == 4) return addr(kb + hh, col0 + L);
+    else if constexpr (ES == 2) return addr(kb + 4 * hh + (L >> 2), col0 + 4 * (L & 3));
     else return addr(kb + 8 * hh + (L >> 1), col0 + 8 * (L & 1));
   }
-  // the fragment at K step ks (h does not change over 32 k-rows)
+  // the fragment at K step ks (h does not change from one to the next)
   static __device__ __forceinline__ typename FragT<ES>::T frag(const lds_u8* tile, const int (&off)[NHH], int ks) {
     typename FragT<ES>::T r;
 #pragma unroll
     for (int hh = 0; hh < NHH; ++hh) {
+      if constexpr (ES == 4) {
+        r[hh] = *(const __attribute__((address_space(3))) unsigned*)(tile + ks * 16 * RB + off[hh]);
+        continue;
+      }
       i32x2 w;
       if constexpr (ES == 2)
         w = __builtin_bit_cast(i32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(

@@ -17,8 +17,8 @@ from tests.gpu_helpers import check, gemm_of, reset_outputs  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
-NAN = {"bf16": 0x7fc0, "f16": 0x7e00, "fp8": 0x7f}
-RAW = {"bf16": np.int16, "f16": np.int16, "fp8": np.uint8}
+NAN = {"bf16": 0x7fc0, "f16": 0x7e00, "fp8": 0x7f, "f32": 0x7fc00000}
+RAW = {"bf16": np.int16, "f16": np.int16, "fp8": np.uint8, "f32": np.int32}
 
 
 @pytest.fixture(scope="module")
@@ -53,7 +53,7 @@ FORMS = [  # m, n, k, padding of A's, B's and C's rows, shift of the bases (elem
     (260, 31, 200, 0, 0, 2, 8), (40, 300, 333, 2, 2, 0, 2), (100, 100, 1000, 0, 3, 7, 5)]
 
 
-@pytest.mark.parametrize("dt", ["bf16", "f16", "fp8"])
+@pytest.mark.parametrize("dt", ["bf16", "f16", "fp8", "f32"])
 @pytest.mark.parametrize("lay", ["nn", "nt", "tn", "tt"])
 def test_forms(ctx, dt, lay):
     names = ["64x64_w2x2_m32", "128x128_w2x2_m32", "16x64_w1x4_m16"]
@@ -72,7 +72,7 @@ def test_forms(ctx, dt, lay):
             check(mat, label=name)
 
 
-@pytest.mark.parametrize("dt,lay", [("bf16", "nn"), ("f16", "tn"), ("fp8", "nt")])
+@pytest.mark.parametrize("dt,lay", [("bf16", "nn"), ("f16", "tn"), ("fp8", "nt"), ("f32", "nn")])
 def test_split_runs_with_a_tail(ctx, dt, lay):
     """K of several split runs whose last one ends inside a chunk."""
     vid = ctx.find(f"{dt}_{lay}_64x64_w2x2_m32_c0")

@@ -31,7 +31,7 @@ SHAPES = [("nn", 300, 1000, 520, 0), ("nt", 77, 512, 1024, 0), ("nt", 1000, 640,
           ("tn", 513, 515, 1040, 1), ("nn", 260, 260, 64, 0)]
 
 
-@pytest.mark.parametrize("dt", ["bf16", "f16", "fp8"])
+@pytest.mark.parametrize("dt", ["bf16", "f16", "fp8", "f32"])
 @pytest.mark.parametrize("count", [2, 5, 10])
 def test_bits_and_values(ctx, dt, count):
     mats = [inputs.materialize(GemmSpec(m, n, k, dt, int(lay[0] == "t"), int(lay[1] == "t"), seed=9500 + i, pad_a=pad,
