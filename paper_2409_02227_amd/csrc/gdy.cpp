@@ -1249,6 +1249,36 @@ hipStream_t slot_stream(const gdy_ctx* ctx, int slot) {
 bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const std::vector<int>& members,
                 KLaunch* L, int* grid);
 
+// Whether a launch of 256 x 256 kernels runs 128-row tiles: twice the work
+// items at kHalfTile of the time each (4096^3 bf16 118 us, 98 on 256 rows), so
+// where the tiles do not fill the CUs once it wins ((512, 12288, 6144) 108 us on
+// 96 tiles, 76 on 192; 3 x (1024, 2048, 4096) 75 and 53).  Estimated time of a
+// launch of T tiles: the longest tile while T <= CUs, else the work over the CUs
+// plus half of the longest tile (the tail).  Rows do not enter an element's sum:
+// the bits are the same.
+const double kHalfTile = 0.6;
+bool use_rows128(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const std::vector<int>& members,
+                 int joint) {
+  double tiles[2] = {}, work[2] = {}, longest = 0;
+  for (int i : members) {
+    if (is_add_variant(ctx, p.variant_of[i])) continue;
+    const Exec e = exec_of(ctx, p.variant_of[i], g[i]);
+    if (joint == 1 || e.family != 2 || ctx->variants[p.variant_of[i]].cap > 0) return false;
+    for (int h = 0; h < 2; ++h) {
+      const int64_t bm = h ? 128 : 256;
+      const double t = (double)((g[i].m + bm - 1) / bm) * (double)((g[i].n + 255) / 256) * std::max(g[i].batch, 1);
+      tiles[h] += t;
+      work[h] += t * (double)g[i].k;
+    }
+    longest = std::max(longest, (double)g[i].k);
+  }
+  auto est = [&](int h) {
+    const double item = h ? kHalfTile : 1.0;
+    return tiles[h] <= ctx->cus ? item * longest : item * (work[h] / ctx->cus + 0.5 * longest);
+  };
+  return est(1) < 0.95 * est(0);
+}
+
 // Workgroup ranges of one dispatch: each GEMM gets its own grid (tiles, or
 // its cap x occupancy), every range but the last rounded up to a multiple
 // of 8 so each GEMM starts on XCD 0 (the extra workgroups find no tile).
@@ -1259,6 +1289,7 @@ gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p,
   L->count = (int)members.size();
   *split = false;
   int64_t wg = 0;
+  const bool rows128 = use_rows128(ctx, g, p, members, joint);
   bool one_tile = true;  // every member runs the same tile
   int tile_m = 0, tile_n = 0;
   for (int u = 0; u < L->count; ++u) {
@@ -1273,6 +1304,10 @@ gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p,
       if (tile_m == 0) tile_m = bm, tile_n = bn;
       if (tile_m != bm || tile_n != bn) one_tile = false;
       a.tiles_m = (int32_t)((g[i].m + bm - 1) / bm);
+      if (rows128) {
+        a.rows128 = 1;
+        a.tiles_m = (int32_t)((g[i].m + 127) / 128);
+      }
       a.tiles_n = (int32_t)((g[i].n + bn - 1) / bn);
       a.code = e.code;
     }
@@ -1647,6 +1682,62 @@ gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
   return st;
 }
 
+// The variant of another input type or layout that stands for `vid`: the same
+// cap on the kernel with the closest tile (log2 of rows and columns), direct for
+// direct where there is a choice.
+int sibling_variant(const gdy_ctx* ctx, int vid, int dtype, int ta, int tb) {
+  if (vid < 0) return -1;
+  const Variant& v = ctx->variants[vid];
+  const KernelDesc* d = ctx->kernels[v.kernel].d;
+  int best = -1;
+  double best_d = 0;
+  for (size_t w = 0; w < ctx->variants.size(); ++w) {
+    const KernelDesc* e = ctx->kernels[ctx->variants[w].kernel].d;
+    if (e->ew || e->dtype != dtype || e->ta != ta || e->tb != tb || ctx->variants[w].cap != v.cap) continue;
+    const double dist = 4.0 * (std::fabs(std::log2((double)e->bm / d->bm)) + std::fabs(std::log2((double)e->bn / d->bn))) +
+                        2.0 * (e->direct != d->direct) + (e->lds_bytes != d->lds_bytes);
+    if (best < 0 || dist < best_d) {
+      best = (int)w;
+      best_d = dist;
+    }
+  }
+  return best;
+}
+
+// Input types and layouts the table holds no tuned shape of borrow those of a
+// sibling, on their own kernels of the same tiles: fp16 and bf16 each other's
+// (the kernels differ in nothing but the MFMA), any type its untransposed ones.
+// The isolated heuristic, which knows neither K nor a kernel's speed, would put
+// them on the smallest tiles: (1023, 1025, 777) fp16 with B stored N x K on
+// 16 x 64 tiles 100 us, on 64 x 64 ones 20.
+void borrow_entries(const gdy_ctx* ctx, Table* t) {
+  std::vector<TableEntry> add;
+  for (int dt = 1; dt <= 4; ++dt)
+    for (int ta = 0; ta < 2; ++ta)
+      for (int tb = 0; tb < 2; ++tb) {
+        if (!t->by_layout[dt][ta][tb].empty()) continue;
+        const int other = dt == DT_F16 ? DT_BF16 : dt == DT_BF16 ? DT_F16 : 0;
+        const std::vector<int>* from = &t->by_layout[other][ta][tb];
+        if (from->empty()) from = &t->by_layout[dt][0][0];
+        if (from->empty() && other) from = &t->by_layout[other][0][0];
+        for (int i : *from) {
+          TableEntry e = t->entries[i];
+          e.dtype = dt;
+          e.ta = ta;
+          e.tb = tb;
+          bool ok = true;
+          for (int& v : e.v) ok = (v = sibling_variant(ctx, v, dt, ta, tb)) >= 0 && ok;
+          for (int& v : e.rc) v = sibling_variant(ctx, v, dt, ta, tb);
+          if (ok) add.push_back(e);
+        }
+      }
+  for (const TableEntry& e : add) {
+    t->by_layout[e.dtype][e.ta][e.tb].push_back((int)t->entries.size());
+    t->keys[e.dtype][e.ta][e.tb].push_back(EntryKey{(double)e.mlog, e.ln, e.lk, e.li});
+    t->entries.push_back(e);
+  }
+}
+
 gdy_status load_table(gdy_ctx* ctx, const char* path) {
   std::ifstream f(path);
   if (!f) return fail(ctx, GDY_ERR_TABLE, "cannot open GO table %s", path);
@@ -1748,6 +1839,7 @@ gdy_status load_table(gdy_ctx* ctx, const char* path) {
     if (seen != 0 && seen != 4) return fail(ctx, GDY_ERR_TABLE, "incomplete predictor block %d", d);
     t.lr[d].has = seen == 4;
   }
+  borrow_entries(ctx, &t);
   t.loaded = true;
   ctx->table = t;
   return GDY_OK;

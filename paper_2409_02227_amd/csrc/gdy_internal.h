@@ -34,6 +34,7 @@ struct KArgs {
   int32_t xcd_remap;  // 1: keep consecutive tiles on one XCD
   int32_t batch;      // items of a strided batch (>= 1); the extents above are per item
   int32_t code;       // joint launches: the member's tile and layout
+  int32_t rows128;    // 256 x 256 kernels: 1: tiles of 128 rows (tiles_m counts them)
   int32_t ew;         // 0: a GEMM; else the DT_* of an element-wise add (C = A + B)
   int32_t split;      // split-K: K tiles are cut into `split` runs of `split_kt` tiles;
   int32_t split_kt;   //   each run writes an fp32 M x N plane, a reduction kernel sums them

@@ -154,8 +154,8 @@ __device__ __forceinline__ void p_tiles(const KArgs& args, int lwg, int nwg, lds
     const Rsrc rc = make_rsrc(p.c + item * p.stride_c, p.c_bytes);
     int tm, tn;
     tile_coords(t, p, tm, tn);
-    const int m0 = tm * 256, n0 = tn * 256;
-    const bool half = Mrows - m0 <= 128;  // a 128-row tile
+    const int m0 = tm * (p.rows128 ? 128 : 256), n0 = tn * 256;
+    const bool half = p.rows128 || Mrows - m0 <= 128;  // a 128-row tile
 
     PhaseCopy<C::ES, TA == 0, JOINT> ca;
     PhaseCopy<C::ES, TB == 1, JOINT> cb;

@@ -91,6 +91,7 @@ __device__ __forceinline__ KArgs uniform(const KArgs& q) {
   p.a_bytes = uniform(q.a_bytes), p.b_bytes = uniform(q.b_bytes), p.c_bytes = uniform(q.c_bytes);
   p.tiles_m = uniform(q.tiles_m), p.tiles_n = uniform(q.tiles_n), p.batch = uniform(q.batch);
   p.c_vec = uniform(q.c_vec), p.a_dma = uniform(q.a_dma), p.b_dma = uniform(q.b_dma);
+  p.rows128 = uniform(q.rows128);
   p.split = uniform(q.split), p.split_kt = uniform(q.split_kt), p.ws = uniform(q.ws);
   p.stride_a = uniform(q.stride_a), p.stride_b = uniform(q.stride_b), p.stride_c = uniform(q.stride_c);
   return p;
