@@ -717,13 +717,17 @@ Exec exec_of(const gdy_ctx* ctx, int vid, const gdy_gemm& g) {
 }
 
 // As a member of a joint launch of `family`: 256 x 256 kernels join 128 x 128
-// ones as 128 x 128 tiles.
+// ones as 128 x 128 tiles, and the other way round (launch_units says when).
 Exec joint_exec(const gdy_ctx* ctx, int vid, const gdy_gemm& g, int family) {
   Exec e = exec_of(ctx, vid, g);
   if (family == 1 && e.family == 2) {
     e.code *= 8;
     e.jbm = e.jbn = 128;
     e.family = 1;
+  } else if (family == 2 && e.family == 1) {
+    e.code /= 8;
+    e.jbm = e.jbn = 256;
+    e.family = 2;
   }
   return e;
 }
@@ -1249,34 +1253,46 @@ hipStream_t slot_stream(const gdy_ctx* ctx, int slot) {
 bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const std::vector<int>& members,
                 KLaunch* L, int* grid);
 
+// Estimated time of a launch whose members all run tiles of bm x bn, in units of
+// a 256 x 256 tile's time for one step of K; `item` is a tile's time and `share`
+// what it takes of a CU (less where several are resident).  The longest tile
+// while every tile is resident, else the work over the CUs plus the tail, half
+// of the shortest tile (which starts last).
+double launch_estimate(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<int>& members, int bm, int bn,
+                       double item, double share) {
+  double tiles = 0, work = 0, longest = 0, shortest = 1e30;
+  for (int i : members) {
+    if (g[i].op != GDY_OP_GEMM) continue;
+    const double t = (double)((g[i].m + bm - 1) / bm) * (double)((g[i].n + bn - 1) / bn) * std::max(g[i].batch, 1);
+    tiles += t;
+    work += t * (double)g[i].k;
+    longest = std::max(longest, (double)g[i].k);
+    shortest = std::min(shortest, (double)g[i].k);
+  }
+  return tiles * share <= ctx->cus * item
+             ? item * longest
+             : std::max(item * longest, share * work / ctx->cus + 0.5 * item * std::min(shortest, longest));
+}
+
 // Whether a launch of 256 x 256 kernels runs 128-row tiles: twice the work
 // items at kHalfTile of the time each (4096^3 bf16 118 us, 98 on 256 rows), so
 // where the tiles do not fill the CUs once it wins ((512, 12288, 6144) 108 us on
-// 96 tiles, 76 on 192; 3 x (1024, 2048, 4096) 75 and 53).  Estimated time of a
-// launch of T tiles: the longest tile while T <= CUs, else the work over the CUs
-// plus half of the longest tile (the tail).  Rows do not enter an element's sum:
-// the bits are the same.
+// 96 tiles, 76 on 192; 3 x (1024, 2048, 4096) 75 and 53).  Rows do not enter an
+// element's sum: the bits are the same.
 const double kHalfTile = 0.6;
+bool rows128_wins(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<int>& members) {
+  return launch_estimate(ctx, g, members, 128, 256, kHalfTile, kHalfTile) <
+         0.95 * launch_estimate(ctx, g, members, 256, 256, 1.0, 1.0);
+}
 bool use_rows128(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const std::vector<int>& members,
                  int joint) {
-  double tiles[2] = {}, work[2] = {}, longest = 0;
   for (int i : members) {
     if (is_add_variant(ctx, p.variant_of[i])) continue;
-    const Exec e = exec_of(ctx, p.variant_of[i], g[i]);
-    if (joint == 1 || e.family != 2 || ctx->variants[p.variant_of[i]].cap > 0) return false;
-    for (int h = 0; h < 2; ++h) {
-      const int64_t bm = h ? 128 : 256;
-      const double t = (double)((g[i].m + bm - 1) / bm) * (double)((g[i].n + 255) / 256) * std::max(g[i].batch, 1);
-      tiles[h] += t;
-      work[h] += t * (double)g[i].k;
-    }
-    longest = std::max(longest, (double)g[i].k);
+    if (joint == 1 || joint_exec(ctx, p.variant_of[i], g[i], joint).family != 2 ||
+        ctx->variants[p.variant_of[i]].cap > 0)
+      return false;
   }
-  auto est = [&](int h) {
-    const double item = h ? kHalfTile : 1.0;
-    return tiles[h] <= ctx->cus ? item * longest : item * (work[h] / ctx->cus + 0.5 * longest);
-  };
-  return est(1) < 0.95 * est(0);
+  return rows128_wins(ctx, g, members);
 }
 
 // Workgroup ranges of one dispatch: each GEMM gets its own grid (tiles, or
@@ -1505,6 +1521,9 @@ struct Unit {
 // quarter longer (4096^3 bf16: 124 us, 100 on 256 x 256), a fork and join
 // 20-25 us, so below kJoinUs of roofline time they join.
 const double kJoinUs = 40.0;
+const double kSmallTile = 0.32;  // a 128 x 128 tile's share of a CU
+const double kForkSteps = 840;   // a fork and join, 20 us, in steps of K of a 16-bit 256 x 256 tile (23.7 ns)
+const int64_t kWidenK = 1024;    // the shortest K that changes to 256 x 256 tiles
 std::vector<Unit> launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
                                const std::vector<int>& ids, const std::vector<std::vector<int>>& members) {
   std::vector<Unit> out;
@@ -1525,6 +1544,39 @@ std::vector<Unit> launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_
     for (size_t u = 0; u < ids.size(); ++u)
       for (size_t q = 0; q < ids.size(); ++q)
         if (family[u] == 2 && family[q] == 1 && dtype[q] == dtype[u]) family[u] = 1;
+  // Dispatches of 128 x 128 tiles (of one type) run on the 256 x 256 kernel,
+  // with the group's others on it, where the estimate says so.  A 128 x 128
+  // tile takes kSmallTile of a 256 x 256 one and a CU holds two of them (4096^3
+  // bf16: 124 us, 97 on 256 x 256).  2 x (2048, 4096, 4096) nt on 256 x 256 tiles
+  // beside 2 x (4096, 4096, 2048) tn on 128 x 128 ones took 264 us, jointly on
+  // 256 x 256 ones 218.  Short K is left alone: the estimate knows no prologue
+  // and no store.
+  for (size_t u = 0; u < ids.size(); ++u) {
+    if (family[u] != 1 || dtype[u] == DT_F32) continue;
+    std::vector<int> small, large, all;
+    bool fits = true;
+    for (size_t q = 0; q < ids.size(); ++q) {
+      if (family[q] == 0 || dtype[q] != dtype[u]) continue;
+      for (int i : members[q]) {
+        (family[q] == 1 ? small : large).push_back(i);
+        all.push_back(i);
+        if (family[q] != 1 || is_add_variant(ctx, p.variant_of[i])) continue;
+        const Exec e = exec_of(ctx, p.variant_of[i], g[i]);
+        fits = fits && e.jbm == 128 && e.jbn == 128 && p.split_of[i] <= 1 && g[i].k >= kWidenK && a_copies(g[i]) &&
+               b_copies(g[i]);
+      }
+    }
+    auto wide = [&](const std::vector<int>& m) {
+      return std::min(launch_estimate(ctx, g, m, 256, 256, 1.0, 1.0),
+                      launch_estimate(ctx, g, m, 128, 256, kHalfTile, kHalfTile));
+    };
+    fits = fits && (int)all.size() <= kMaxFused;
+    double apart = launch_estimate(ctx, g, small, 128, 128, 2 * kSmallTile, kSmallTile);
+    if (!large.empty()) apart += wide(large) + (dtype[u] == DT_FP8 ? 2 : 1) * kForkSteps;
+    if (fits && wide(all) < 0.9 * apart)
+      for (size_t q = 0; q < ids.size(); ++q)
+        if (family[q] == 1 && dtype[q] == dtype[u]) family[q] = 2;
+  }
   std::vector<size_t> first;  // the dispatch that opened each launch
   for (size_t u = 0; u < ids.size(); ++u) {
     size_t q = 0;
@@ -1539,6 +1591,16 @@ std::vector<Unit> launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_
     }
     out[q].ids.push_back(ids[u]);
     out[q].members.insert(out[q].members.end(), members[u].begin(), members[u].end());
+  }
+  // a launch of one dispatch runs jointly where that changes its tiles
+  for (size_t q = 0; q < out.size(); ++q) {
+    const size_t u = first[q];
+    if (out[q].joint || family[u] == 0) continue;
+    for (int i : out[q].members) {
+      if (is_add_variant(ctx, p.variant_of[i])) continue;
+      const Exec e = exec_of(ctx, p.variant_of[i], g[i]);
+      if (e.family != family[u]) out[q].joint = family[u];
+    }
   }
   // the longest work items first, as within a dispatch; adds last
   for (Unit& x : out)

@@ -101,3 +101,76 @@ def test_table_bound_kernels_join(ctx, tmp_path):
             assert np.array_equal(out_codes(m), bits), m.spec.name
     finally:
         t.close()
+
+
+def bound_table(path, ctx, rows, name):
+    """A GO table that binds each row (dtype code, layout, m, n, k) to the kernel `name` of its type and layout."""
+    lines = ["gdy-go-table 2", f"device gfx950 cus {ctx.cus()}", f"catalogue {ctx.catalogue_hash():016x}"]
+    codes = {"f16": 1, "bf16": 2, "fp8": 3, "f32": 4}
+    for dt, lay, m, n, k in rows:
+        ta, tb = int(lay[0] == "t"), int(lay[1] == "t")
+        lines.append(f"entry {codes[dt]} {ta} {tb} {(m - 1).bit_length()} {n} {k} 1 " +
+                     " ".join([f"{dt}_{lay}_{name}_c0"] * 5))
+    path.write_text("\n".join(lines) + "\n")
+    return str(path)
+
+
+def same_bits_alone(t, mats, plan):
+    got = [out_codes(m).copy() for m in mats]
+    for m, v, bits in zip(mats, plan["variant_of"], got):
+        reset_outputs([m])
+        t.execute([gemm_of(m, v)], mode="forced")
+        torch.cuda.synchronize()
+        assert np.array_equal(out_codes(m), bits), m.spec.name
+
+
+@pytest.mark.parametrize("dt,k", [("bf16", 1032), ("f16", 1088), ("fp8", 2064)])
+@pytest.mark.parametrize("layouts", [("nt", "tn"), ("nn", "nn"), ("tt", "tn")])
+def test_wide_tiles_for_128_row_kernels(ctx, tmp_path, dt, k, layouts):
+    """Large groups bound to 128 x 128 kernels run on the 256 x 256 one: one
+    launch of a quarter of the tiles, the bits of the kernels alone."""
+    rows = [(dt, lay, 2048, 4096 - 16 * i, k) for i, lay in enumerate(layouts)]
+    t = gdy.Context(0, table=bound_table(tmp_path / "wide.table", ctx, rows, "128x128_w2x2_m32"))
+    try:
+        mats = [inputs.materialize(GemmSpec(m, n, kk, dt, int(lay[0] == "t"), int(lay[1] == "t"), seed=9800 + i,
+                                            name=f"{dt}_{lay}_{m}x{n}x{kk}"))
+                for i, (_, lay, m, n, kk) in enumerate(rows)]
+        gemms = [gemm_of(m) for m in mats]
+        reset_outputs(mats)
+        plan = t.execute(gemms, mode="go", want_plan=True)
+        torch.cuda.synchronize()
+        assert set(plan["stream_of"]) == {-1}
+        assert t.dispatch_map(gemms, mode="go")["grid"] <= 256 + 8
+        same_bits_alone(t, mats, plan)
+    finally:
+        t.close()
+
+
+@pytest.mark.parametrize("dt", ["bf16", "fp8"])
+@pytest.mark.parametrize("m,n,k", [(1300, 4096, 1040), (513, 12288, 1040), (2048, 1024, 1040), (1024, 2048, 1040)])
+def test_half_rows(ctx, tmp_path, dt, m, n, k):
+    """256 x 256 launches that do not fill the chip cut their tile rows in two
+    (whole, short and one-row last tiles), others do not; the bits are those of
+    the 128 x 128 kernel."""
+    rows = [(dt, "nn", m, n, k)]
+    mat = inputs.materialize(GemmSpec(m, n, k, dt, 0, 0, seed=9900 + m, name=f"{dt}_{m}x{n}x{k}"))
+    got = {}
+    for name in ("256x256_w2x4_m32", "128x128_w2x2_m32"):
+        t = gdy.Context(0, table=bound_table(tmp_path / f"{name}.table", ctx, rows, name))
+        try:
+            reset_outputs([mat])
+            vid = t.find(f"{dt}_nn_{name}_c0") if name[0] == "1" else None
+            plan = t.execute([gemm_of(mat) if vid is None else gemm_of(mat, vid)],
+                             mode="go" if vid is None else "forced", want_plan=True)
+            torch.cuda.synchronize()
+            got[name] = out_codes(mat).copy()
+            assert plan["split_of"][0] == 1
+            if name[0] == "2":
+                full, half = -(-m // 256) * -(-n // 256), -(-m // 128) * -(-n // 256)
+                # the estimates at one K: 1 and 0.6 of a tile's time while they fit, else work and half a tile
+                cost = lambda x, t: t if x <= ctx.cus() else t * (x / ctx.cus() + 0.5)  # noqa: E731
+                want = half if cost(half, 0.6) < 0.95 * cost(full, 1.0) else full
+                assert t.dispatch_map([gemm_of(mat)], mode="go")["grid"] == want
+        finally:
+            t.close()
+    assert np.array_equal(*got.values())
