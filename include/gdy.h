@@ -107,7 +107,8 @@ typedef enum {
  * in an isolated launch, so results are bit-identical.  In GO and SELECTOR,
  * dispatches of a group whose kernels belong to one family (256 x 256 tiles;
  * smaller ones) and input type run jointly in one kernel launch, each GEMM on
- * the code of its own kernel, with the same bits: the plan still counts a
+ * tiles of its own kernel's size or, where that is estimated to be faster, of
+ * the other family's, with the same bits: the plan still counts a
  * dispatch per kernel, and they share a stream slot and, in the timings, an
  * interval.  SEQUENTIAL, DEFAULT and FORCED launch one dispatch per GEMM.
  */
