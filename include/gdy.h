@@ -149,7 +149,9 @@ typedef struct {
   int32_t n;                            /* GEMMs planned                                   */
   int32_t cd;                           /* largest number of GEMMs launched together       */
   int32_t n_groups;                     /* groups run one after another                    */
-  int32_t fallback;                     /* 1: no usable GO table, isolated heuristics used  */
+  int32_t fallback;                     /* 1: no usable GO table (isolated heuristics), or a
+                                           GEMM whose type and layout it holds no shape of
+                                           (kernels of a sibling's shapes, see gdy_create)  */
   int32_t order[GDY_MAX_GEMMS];         /* launch order: order[t] is a GEMM index          */
   int32_t group_of[GDY_MAX_GEMMS];      /* group of GEMM i                                 */
   int32_t stream_of[GDY_MAX_GEMMS];     /* pool stream slot of GEMM i's dispatch (-1: origin) */
@@ -214,7 +216,11 @@ typedef struct gdy_ctx gdy_ctx;
  * returns GDY_OK: SELECTOR and GO modes fall back to isolated heuristics
  * (every GEMM at CD 1, i.e. isolated kernels one after another, Sec. 5.5's
  * sequential configuration) and every plan reports fallback = 1;
- * gdy_last_error() gives the reason until the next call.
+ * gdy_last_error() gives the reason until the next call.  A GEMM whose input
+ * type and layout a usable table holds no shape of binds the kernels tuned for
+ * a sibling (fp16 and bf16 for each other, else the type's untransposed
+ * layout), on its own kernels of the closest tiles; its plans report fallback =
+ * 1 too.  With nothing to borrow it runs its isolated heuristic.
  * `use_cu_masks` is a bit set: bit 0 creates one CU-masked stream for each
  * resource constraint GPU/2, GPU/4 and GPU/8 (isolated runs of the tuner);
  * bit 1 creates the CU-Partition streams (2 + 4 + 8 streams whose masks

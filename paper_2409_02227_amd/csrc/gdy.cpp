@@ -64,6 +64,7 @@ struct TableEntry {
   double ln, lk;  // log2(n), log2(k)
   int64_t items = 1;  // batch items of the tuned shape (a B-GEMM's count; 1: a single GEMM)
   double li = 0.0;    // log2(items)
+  bool borrowed = false;  // not in the table: borrow_entries made it from a sibling's
   int v[GDY_N_CD];
   int rc[3] = {-1, -1, -1};  // best kernel tuned under kRcBudgets[r] CUs (-1: not in the table)
 };
@@ -278,12 +279,12 @@ int nearest_entry(const gdy_ctx* ctx, const gdy_gemm& g) {
 }
 
 // Variant for CD class ci given the GEMM's nearest tuned entry (-1: none,
-// then the isolated heuristics).
+// then the isolated heuristics).  A borrowed entry binds, but the table holds
+// no tuned shape of the GEMM's type and layout: the plan still says so.
 int bind_entry(const gdy_ctx* ctx, const gdy_gemm& g, int entry, int ci, bool* fallback) {
   if (g.op == GDY_OP_ADD) return heuristic_variant(ctx, g);  // the add kernel of its type
-  if (entry >= 0) return runnable(ctx, ctx->table.entries[entry].v[ci], g);
-  if (fallback) *fallback = true;
-  return heuristic_variant(ctx, g);
+  if (fallback && (entry < 0 || ctx->table.entries[entry].borrowed)) *fallback = true;
+  return entry >= 0 ? runnable(ctx, ctx->table.entries[entry].v[ci], g) : heuristic_variant(ctx, g);
 }
 
 int bind_variant(const gdy_ctx* ctx, const gdy_gemm& g, int ci, bool* fallback) {
@@ -310,8 +311,10 @@ int class_for_size(int s) {
 int bind_partition(const gdy_ctx* ctx, const gdy_gemm& g, int r, bool* fallback) {
   if (g.op == GDY_OP_ADD) return heuristic_variant(ctx, g);
   const int entry = nearest_entry(ctx, g);
-  if (entry >= 0 && ctx->table.entries[entry].rc[r] >= 0)
+  if (entry >= 0 && ctx->table.entries[entry].rc[r] >= 0) {
+    if (fallback && ctx->table.entries[entry].borrowed) *fallback = true;
     return runnable(ctx, ctx->table.entries[entry].rc[r], g);
+  }
   return bind_entry(ctx, g, entry, class_for_size(kParts[r]), fallback);
 }
 
@@ -1784,6 +1787,7 @@ void borrow_entries(const gdy_ctx* ctx, Table* t) {
         if (from->empty() && other) from = &t->by_layout[other][0][0];
         for (int i : *from) {
           TableEntry e = t->entries[i];
+          e.borrowed = true;
           e.dtype = dt;
           e.ta = ta;
           e.tb = tb;
