@@ -40,6 +40,7 @@ const int kMaxSplit = 16;
 const int kMinSplitKTiles = 16;                // K tiles per run at least
 const int64_t kSplitMemberBytes = 16LL << 20;  // fp32 partial planes of one GEMM at most
 const int64_t kSplitWsBytes = 256LL << 20;     // workspace of a context
+const int kTileKBytes = 128;                   // K bytes of a row that the tile loops take at a time
 const int kSplitMaxTile = 128 * 128;           // larger tiles' split twins spill registers
 
 struct Kernel {
@@ -1359,7 +1360,10 @@ gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p,
 // workgroup b to XCD b % 8, and each XCD's L2 fetches whatever its
 // workgroups read.  Spread over all eight, every member's A is fetched eight
 // times.  Instead, the members' work items are laid out per K length (one
-// line per distinct number of K tiles, longest first) and each line is cut
+// line per distinct number of K tiles (of what every kernel's loop takes, not
+// of the bk a name states: names of one kernel state 64 and 128 bytes, which put
+// members of one K on two lines and left the busiest XCD up to 16% over its
+// share), longest first) and each line is cut
 // into eight contiguous pieces, one per XCD, whose lengths even out the XCDs'
 // total work (tiles x (K tiles + 1, the store)); cuts keep a tile column's
 // rows together (multiples of min(tile rows, 8) within a member, the rows
@@ -1379,7 +1383,7 @@ bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, cons
     if (g[i].op != GDY_OP_GEMM || d->ew || p.split_of[i] > 1 || v.cap > 0) return false;
     tiles[u] = (int64_t)L->g[u].tiles_m * L->g[u].tiles_n * std::max(L->g[u].batch, 1);
     if (tiles[u] <= 0 || tiles[u] >= (1LL << 29)) return false;
-    nk[u] = (g[i].k + d->bk - 1) / d->bk;
+    nk[u] = (g[i].k * elem_size(g[i].a_type) + kTileKBytes - 1) / kTileKBytes;
     unit[u] = std::min<int64_t>(L->g[u].tiles_m, L->g[u].group_m);
   }
   std::vector<int64_t> ks(nk.begin(), nk.end());

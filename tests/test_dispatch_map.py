@@ -115,3 +115,38 @@ def test_every_dispatch_covers_its_work_once():
                 _, placed = _check_cover(ctx, descs, mode, forced)
                 placed_total += placed
     assert placed_total > 0  # some fused dispatches were placed
+
+
+@pytest.mark.parametrize("dtype,name,tile_k", [(3, "fp8", 128), (2, "bf16", 64)])
+def test_placement_counts_the_k_tiles_that_run(dtype, name, tile_k):
+    """Names of the one 256 x 256 kernel that state K tiles of 64 and of 128
+    bytes share a dispatch: members of one K weigh the same, so XCDs hold equal
+    work.  Four members of 8 x 32 tiles of one K: 128 tiles on each XCD.  Random
+    sets: the busiest XCD is within 3% of its share on average (a cut falls
+    on whole tile columns); 10-17% when K tiles were counted by name."""
+    ctx = gdy.Context(-1)
+    kern = [ctx.find(f"{name}_nn_256x256_{s}_c0") for s in ("w2x4_d4h", "w2x4_d2", "w2x2_d4h", "w2x2_d2")]
+
+    def work(sizes, variants):
+        descs = [_desc(m, n, k, dtype, j) for j, (m, n, k) in enumerate(sizes)]
+        for d, v in zip(descs, variants):
+            d.variant = v
+        assert ctx.plan(descs, mode="forced_grouped")["n_dispatches"] == 1
+        m = ctx.dispatch_map(descs, mode="forced_grouped", dispatch=0)
+        out = np.zeros(8)
+        for b, g in enumerate(m["gemm"][:m["grid"]]):
+            if g >= 0:
+                out[b % 8] += sizes[g][2] // tile_k + 1
+        return out
+
+    w = work([(2048, 8192, 4096)] * 4, kern)
+    assert w.min() == w.max() == 128 * (4096 // tile_k + 1)
+    rng = np.random.default_rng(5)
+    over = []
+    for _ in range(40):
+        u = int(rng.integers(2, 13))
+        sizes = [tuple(int(rng.choice(c)) for c in ((512, 1024, 2048), (2048, 4096, 8192), (2048, 4096, 8192)))
+                 for _ in range(u)]
+        w = work(sizes, [kern[int(rng.integers(2))] for _ in range(u)])
+        over.append(w.max() / w.mean() - 1)
+    assert np.mean(over) < 0.03, np.mean(over)
