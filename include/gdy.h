@@ -247,7 +247,8 @@ gdy_status gdy_create(gdy_ctx** out, int device, const char* table_path, int32_t
  * the CU-masked streams restricted to that many CUs (needs use_cu_masks
  * bit 0 at create).  Pool streams carry every dispatch of GDY_DEFAULT and
  * GDY_FORCED (the tuner's isolated runs use GDY_FORCED with forced_cd 1)
- * and the further dispatches of a group; what runs on the caller's origin
+ * and the further dispatches of a group (which therefore do not run jointly
+ * with the first under a budget); what runs on the caller's origin
  * stream (GDY_SEQUENTIAL, a group's first dispatch) is not masked.  Other
  * values: GDY_ERR_INVALID_ARG.
  */

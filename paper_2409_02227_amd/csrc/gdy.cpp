@@ -1517,6 +1517,13 @@ struct Unit {
   int joint = 0;             // its family, 0: one dispatch on its own kernel
 };
 
+// The modes whose groups run dispatches jointly.  Not under a CU budget: a joint
+// launch runs on the origin stream, and the budget masks a group's further
+// dispatches, which run on pool streams.
+bool joint_mode(const gdy_ctx* ctx, int mode) {
+  return (mode == GDY_SELECTOR || mode == GDY_GO) && ctx->rc == 0;
+}
+
 // The launches of one group's dispatches (ids, in launch order, and their
 // members).  In the modes that choose kernels by group, dispatches whose kernels
 // belong to one family and input type join the first of them that has room
@@ -1545,7 +1552,7 @@ std::vector<Unit> launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_
       if (ctx->variants[p.variant_of[i]].cap > 0) capped = true;
       if (family[u] == 2) large_s += roofline_s(g[i]);
     }
-    if (capped || (mode != GDY_SELECTOR && mode != GDY_GO)) family[u] = 0;
+    if (capped || !joint_mode(ctx, mode)) family[u] = 0;
   }
   if (large_s < kJoinUs * 1e-6)
     for (size_t u = 0; u < ids.size(); ++u)
@@ -1642,7 +1649,7 @@ void group_dispatches(const gdy_plan_t& p, int grp, std::vector<int>* ids, std::
 // Streams of the joint modes' launches: a group's first launch on the origin
 // stream, the others round-robin on the pool.
 void plan_units(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode) {
-  if ((mode != GDY_SELECTOR && mode != GDY_GO) || p->n_dispatches <= p->n_groups) return;
+  if (!joint_mode(ctx, mode) || p->n_dispatches <= p->n_groups) return;
   const int S = std::max(pool_size(ctx), 1);
   for (int grp = 0; grp < p->n_groups; ++grp) {
     std::vector<int> ids;

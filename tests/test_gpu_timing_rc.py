@@ -131,3 +131,39 @@ def test_last_kernel_times_match_the_timing_ring(rctx):
         assert lib.gdy_last_kernel_times(rctx.h, None, f4(), n) == 1  # NULL pointer
     finally:
         rctx.set_timing(False)
+
+
+def test_budget_masks_the_further_dispatches_of_a_group(tmp_path):
+    """A GO group of two kernels that run jointly on the whole GPU: under a
+    budget the second dispatch keeps a masked pool stream, with the same bits,
+    and takes several times longer on an eighth of the CUs."""
+    lines = ["gdy-go-table 2", "device gfx950 cus 256", "catalogue 0"]
+    lines += [f"entry 2 0 0 {m.bit_length() - 1} {n} {k} 1 " + " ".join([f"bf16_nn_{name}_c0"] * 5)
+              for m, n, k, name in ((4096, 4096, 4096, "128x128_w2x2_d2"), (1024, 4096, 1024, "64x64_w2x2_d4"))]
+    path = tmp_path / "rc.table"
+    path.write_text("\n".join(lines) + "\n")
+    c = gdy.Context(0, table=str(path), max_streams=4, use_cu_masks=gdy.RC_STREAMS)
+    try:
+        gemms = [gdy.Gemm(*_operands(m, n, k, 60 + j), torch.empty(m, n, dtype=torch.bfloat16, device="cuda"))
+                 for j, (m, n, k) in enumerate([(1024, 4096, 1024), (4096, 4096, 4096)])]
+        out, streams, times = {}, {}, {}
+        for rc in (0, 32):
+            c.set_rc(rc)
+            for g in gemms:
+                g.c.fill_(float("nan"))
+            plan = c.execute(gemms, mode="go", want_plan=True)
+            torch.cuda.synchronize()
+            assert [c.variant(v)["name"] for v in plan["variant_of"][:2]] == ["bf16_nn_64x64_w2x2_d4_c0",
+                                                                             "bf16_nn_128x128_w2x2_d2_c0"]
+            assert plan["n_dispatches"] == 2 and plan["fallback"] == 0
+            streams[rc] = plan["stream_of"][:2]
+            out[rc] = [g.c.clone() for g in gemms]
+            times[rc] = _wall(c, gemms, "go")
+        c.set_rc(0)
+        print(streams, times, flush=True)
+        assert streams == {0: [-1, -1], 32: [-1, 0]}
+        assert all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(out[0], out[32]))
+        assert not any(torch.isnan(x.float()).any() for x in out[32])
+        assert times[32] > 2.0 * times[0], times
+    finally:
+        c.close()
