@@ -1262,8 +1262,8 @@ bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, cons
 // what it takes of a CU (less where several are resident).  The longest tile
 // while every tile is resident, else the work over the CUs plus the tail, half
 // of the shortest tile (which starts last).
-double launch_estimate(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<int>& members, int bm, int bn,
-                       double item, double share) {
+double launch_estimate(int cus, const gdy_gemm* g, const std::vector<int>& members, int bm, int bn, double item,
+                       double share) {
   double tiles = 0, work = 0, longest = 0, shortest = 1e30;
   for (int i : members) {
     if (g[i].op != GDY_OP_GEMM) continue;
@@ -1273,9 +1273,9 @@ double launch_estimate(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<
     longest = std::max(longest, (double)g[i].k);
     shortest = std::min(shortest, (double)g[i].k);
   }
-  return tiles * share <= ctx->cus * item
+  return tiles * share <= cus * item
              ? item * longest
-             : std::max(item * longest, share * work / ctx->cus + 0.5 * item * std::min(shortest, longest));
+             : std::max(item * longest, share * work / cus + 0.5 * item * std::min(shortest, longest));
 }
 
 // Whether a launch of 256 x 256 kernels runs 128-row tiles: twice the work
@@ -1284,32 +1284,38 @@ double launch_estimate(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<
 // 96 tiles, 76 on 192; 3 x (1024, 2048, 4096) 75 and 53).  Rows do not enter an
 // element's sum: the bits are the same.
 const double kHalfTile = 0.6;
-bool rows128_wins(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<int>& members) {
-  return launch_estimate(ctx, g, members, 128, 256, kHalfTile, kHalfTile) <
-         0.95 * launch_estimate(ctx, g, members, 256, 256, 1.0, 1.0);
+bool rows128_wins(int cus, const gdy_gemm* g, const std::vector<int>& members) {
+  return launch_estimate(cus, g, members, 128, 256, kHalfTile, kHalfTile) <
+         0.95 * launch_estimate(cus, g, members, 256, 256, 1.0, 1.0);
 }
-bool use_rows128(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const std::vector<int>& members,
-                 int joint) {
+// The CUs of the stream a launch runs on: a partition's, the active budget's
+// (pool streams only), or all.
+int launch_cus(const gdy_ctx* ctx, const gdy_plan_t& p, int mode, int stream) {
+  if (partition_mode(mode)) return ctx->cus / kParts[partition_index(p.cd, 0)];
+  return ctx->rc > 0 && stream >= 0 ? std::min(ctx->rc, ctx->cus) : ctx->cus;
+}
+bool use_rows128(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
+                 const std::vector<int>& members, int joint) {
   for (int i : members) {
     if (is_add_variant(ctx, p.variant_of[i])) continue;
     if (joint == 1 || joint_exec(ctx, p.variant_of[i], g[i], joint).family != 2 ||
         ctx->variants[p.variant_of[i]].cap > 0)
       return false;
   }
-  return rows128_wins(ctx, g, members);
+  return rows128_wins(launch_cus(ctx, p, mode, p.stream_of[members[0]]), g, members);
 }
 
 // Workgroup ranges of one dispatch: each GEMM gets its own grid (tiles, or
 // its cap x occupancy), every range but the last rounded up to a multiple
 // of 8 so each GEMM starts on XCD 0 (the extra workgroups find no tile).
-gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p,
+gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
                         const std::vector<int>& members, int joint, const std::vector<int64_t>& ws_off,
                         float* ws_base, int64_t ws_cap, KLaunch* L, int* grid, bool* split) {
   std::memset(L, 0, sizeof *L);
   L->count = (int)members.size();
   *split = false;
   int64_t wg = 0;
-  const bool rows128 = use_rows128(ctx, g, p, members, joint);
+  const bool rows128 = use_rows128(ctx, g, p, mode, members, joint);
   bool one_tile = true;  // every member runs the same tile
   int tile_m = 0, tile_n = 0;
   for (int u = 0; u < L->count; ++u) {
@@ -1581,11 +1587,11 @@ std::vector<Unit> launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_
       }
     }
     auto wide = [&](const std::vector<int>& m) {
-      return std::min(launch_estimate(ctx, g, m, 256, 256, 1.0, 1.0),
-                      launch_estimate(ctx, g, m, 128, 256, kHalfTile, kHalfTile));
+      return std::min(launch_estimate(ctx->cus, g, m, 256, 256, 1.0, 1.0),
+                      launch_estimate(ctx->cus, g, m, 128, 256, kHalfTile, kHalfTile));
     };
     fits = fits && (int)all.size() <= kMaxFused;
-    double apart = launch_estimate(ctx, g, small, 128, 128, 2 * kSmallTile, kSmallTile);
+    double apart = launch_estimate(ctx->cus, g, small, 128, 128, 2 * kSmallTile, kSmallTile);
     if (!large.empty()) apart += wide(large) + (dtype[u] == DT_FP8 ? 2 : 1) * kForkSteps;
     if (fits && wide(all) < 0.9 * apart)
       for (size_t q = 0; q < ids.size(); ++q)
@@ -1721,7 +1727,7 @@ gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
       KLaunch launch;
       int grid = 0;
       bool split = false;
-      st = build_launch(ctx, g, p, x.members, x.joint, ws_off, ws_base, ws_cap, &launch, &grid, &split);
+      st = build_launch(ctx, g, p, mode, x.members, x.joint, ws_off, ws_base, ws_cap, &launch, &grid, &split);
       if (st != GDY_OK) break;
       void* argv[] = {&launch};
       const int d = x.ids[0];
@@ -2299,7 +2305,7 @@ gdy_status gdy_dispatch_map(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int3
     int g = 0;
     bool split = false;
     // the planes' base is never dereferenced here
-    s = build_launch(ctx, gemms, p, members, joint, ws_off, reinterpret_cast<float*>(256), kSplitWsBytes, &L, &g, &split);
+    s = build_launch(ctx, gemms, p, mode, members, joint, ws_off, reinterpret_cast<float*>(256), kSplitWsBytes, &L, &g, &split);
     if (s != GDY_OK) return s;
     *grid = g;
     for (int i = 0; i < n; ++i) items_of_gemm[i] = 0;

@@ -150,3 +150,25 @@ def test_placement_counts_the_k_tiles_that_run(dtype, name, tile_k):
         w = work(sizes, [kern[int(rng.integers(2))] for _ in range(u)])
         over.append(w.max() / w.mean() - 1)
     assert np.mean(over) < 0.03, np.mean(over)
+
+
+def test_half_rows_count_the_cus_of_the_stream(tmp_path):
+    """256 x 256 kernels cut their tile rows in two where the tiles do not fill
+    the CUs of the stream they run on: 8 x 8 tiles of (2048, 2048) do not fill
+    256 CUs (0.6 of a tile's time on 128 half tiles against 1), but a quarter
+    of them: 64 tiles on 64 CUs take 1, 128 half tiles 0.6 * 128 / 64 + 0.3.
+    2 x 8 tiles of (512, 2048) fill neither."""
+    name = "bf16_nn_256x256_w2x4_d2_c0"
+    lines = ["gdy-go-table 2", "device host cus 256", "catalogue 0"]
+    lines += [f"entry 2 0 0 {m.bit_length() - 1} 2048 1024 1 " + " ".join([name] * 8) for m in (2048, 512)]
+    path = tmp_path / "half.table"
+    path.write_text("\n".join(lines) + "\n")
+    ctx = gdy.Context(-1, table=str(path))
+    for m, whole_gpu, quarter in ((2048, 128, 64), (512, 32, 32)):
+        descs = [_desc(m, 2048, 1024, 2, j) for j in range(4)]
+        assert ctx.dispatch_map(descs, mode="sequential", dispatch=0)["grid"] == whole_gpu
+        for mode in ("cu_partition", "cu_partition_go", "cu_partition_rc"):
+            p = ctx.plan(descs, mode=mode, forced_cd=4)
+            assert [ctx.variant(v)["name"] for v in p["variant_of"][:4]] == [name] * 4
+            for d in range(4):
+                assert ctx.dispatch_map(descs, mode=mode, forced_cd=4, dispatch=d)["grid"] == quarter

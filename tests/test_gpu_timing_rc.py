@@ -71,6 +71,15 @@ def test_rc_pools_compute_the_same_bits_on_fewer_cus(rctx):
         out[rc] = c
         times[rc] = _wall(rctx, gemm, "forced", forced_cd=1)
         print(f"rc {rc}: {times[rc] * 1e6:.0f} us", flush=True)
+    # 128-row tiles where they fit the budget's CUs: 64 whole tiles or 128 half ones
+    half = [gdy.Gemm(a[:2048], b[:, :2048], out[0][:2048, :2048], variant=vid)]
+    for rc, grid in ((0, 128), (128, 128), (64, 64), (32, 64)):
+        rctx.set_rc(rc)
+        assert rctx.dispatch_map(half, mode="forced", forced_cd=1)["grid"] == grid
+        if rc:  # the origin stream is not masked
+            assert rctx.dispatch_map([gdy.Gemm(g.a, g.b, g.c) for g in half], mode="sequential")["grid"] == seq_grid
+        else:
+            seq_grid = rctx.dispatch_map([gdy.Gemm(g.a, g.b, g.c) for g in half], mode="sequential")["grid"]
     # the origin stream is not masked: the sequential mode under rc 32 runs at full speed
     seq = _wall(rctx, [gdy.Gemm(a, b, out[0], variant=vid)], "sequential")
     rctx.set_rc(0)
