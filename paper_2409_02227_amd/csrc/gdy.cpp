@@ -623,7 +623,7 @@ gdy_status validate(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int32_t mode
   if (n > 0 && !gemms) return fail(ctx, GDY_ERR_INVALID_ARG, "null gemm array");
   if (mode < GDY_SEQUENTIAL || mode > GDY_CU_PARTITION_RC)
     return fail(ctx, GDY_ERR_INVALID_ARG, "bad mode %d", mode);
-  std::vector<Extent> ea(n), eb(n), ec(n);
+  Extent ea[GDY_MAX_GEMMS], eb[GDY_MAX_GEMMS], ec[GDY_MAX_GEMMS];
   for (int i = 0; i < n; ++i) {
     gdy_status s = validate_one(ctx, gemms[i], i, &ea[i], &eb[i], &ec[i]);
     if (s != GDY_OK) return s;
@@ -939,13 +939,14 @@ void plan_splits(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode)
 
 void make_plan_core(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int forced_cd,
                     gdy_plan_t* p);
-void plan_units(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode);
+struct Launches;
+void plan_units(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode, Launches* out);
 
 void make_plan(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int forced_cd,
-               gdy_plan_t* p) {
+               gdy_plan_t* p, Launches* launches) {
   make_plan_core(ctx, g, n, mode, forced_cd, p);
   plan_splits(ctx, g, p, mode);
-  plan_units(ctx, g, p, mode);
+  plan_units(ctx, g, p, mode, launches);
 }
 
 void make_plan_core(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int forced_cd,
@@ -1254,7 +1255,19 @@ hipStream_t slot_stream(const gdy_ctx* ctx, int slot) {
   return ctx->pool[slot];
 }
 
-bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const std::vector<int>& members,
+// GEMMs (and adds) of one launch, by submission index.
+struct Members {
+  const int* v;
+  int n;
+  Members(const int* first, int count) : v(first), n(count) {}
+  Members(const std::vector<int>& x) : v(x.data()), n((int)x.size()) {}
+  const int* begin() const { return v; }
+  const int* end() const { return v + n; }
+  int size() const { return n; }
+  int operator[](int u) const { return v[u]; }
+};
+
+bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const Members& members,
                 KLaunch* L, int* grid);
 
 // Estimated time of a launch whose members all run tiles of bm x bn, in units of
@@ -1262,7 +1275,7 @@ bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, cons
 // what it takes of a CU (less where several are resident).  The longest tile
 // while every tile is resident, else the work over the CUs plus the tail, half
 // of the shortest tile (which starts last).
-double launch_estimate(int cus, const gdy_gemm* g, const std::vector<int>& members, int bm, int bn, double item,
+double launch_estimate(int cus, const gdy_gemm* g, const Members& members, int bm, int bn, double item,
                        double share) {
   double tiles = 0, work = 0, longest = 0, shortest = 1e30;
   for (int i : members) {
@@ -1284,7 +1297,7 @@ double launch_estimate(int cus, const gdy_gemm* g, const std::vector<int>& membe
 // 96 tiles, 76 on 192; 3 x (1024, 2048, 4096) 75 and 53).  Rows do not enter an
 // element's sum: the bits are the same.
 const double kHalfTile = 0.6;
-bool rows128_wins(int cus, const gdy_gemm* g, const std::vector<int>& members) {
+bool rows128_wins(int cus, const gdy_gemm* g, const Members& members) {
   return launch_estimate(cus, g, members, 128, 256, kHalfTile, kHalfTile) <
          0.95 * launch_estimate(cus, g, members, 256, 256, 1.0, 1.0);
 }
@@ -1295,7 +1308,7 @@ int launch_cus(const gdy_ctx* ctx, const gdy_plan_t& p, int mode, int stream) {
   return ctx->rc > 0 && stream >= 0 ? std::min(ctx->rc, ctx->cus) : ctx->cus;
 }
 bool use_rows128(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
-                 const std::vector<int>& members, int joint) {
+                 const Members& members, int joint) {
   for (int i : members) {
     if (is_add_variant(ctx, p.variant_of[i])) continue;
     if (joint == 1 || joint_exec(ctx, p.variant_of[i], g[i], joint).family != 2 ||
@@ -1309,10 +1322,11 @@ bool use_rows128(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
 // its cap x occupancy), every range but the last rounded up to a multiple
 // of 8 so each GEMM starts on XCD 0 (the extra workgroups find no tile).
 gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
-                        const std::vector<int>& members, int joint, const std::vector<int64_t>& ws_off,
+                        const Members& members, int joint, const std::vector<int64_t>& ws_off,
                         float* ws_base, int64_t ws_cap, KLaunch* L, int* grid, bool* split) {
-  std::memset(L, 0, sizeof *L);
-  L->count = (int)members.size();
+  // of an unplaced block the kernels read count, first, placed and g[0 .. count)
+  L->count = members.size();
+  L->placed = 0;
   *split = false;
   int64_t wg = 0;
   const bool rows128 = use_rows128(ctx, g, p, mode, members, joint);
@@ -1377,7 +1391,7 @@ gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, in
 // holds the same mix of long and short tiles as before -- its CUs pack them
 // as well -- from a few members instead of all.  Only GEMM members that
 // neither split nor cap their grid are placed; anything else keeps ranges.
-bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const std::vector<int>& members,
+bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const Members& members,
                 KLaunch* L, int* grid) {
   const int U = L->count;
   if (U < 2 || !ctx->xcd_place) return false;
@@ -1467,7 +1481,7 @@ bool place_xcds(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, cons
 // Launch block of the split-K reduction for the split members of one GEMM
 // dispatch (their KArgs as built for it): each gets tiles of 8 rows x 128
 // columns over every batch item, ranges rounded to multiples of 8.
-void build_reduce(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const std::vector<int>& members,
+void build_reduce(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const Members& members,
                   const KLaunch& gemm, KLaunch* R, int* grid) {
   (void)ctx;
   std::memset(R, 0, sizeof *R);
@@ -1507,20 +1521,26 @@ std::vector<int64_t> ws_offsets(const gdy_gemm* g, const gdy_plan_t& p, int mode
   return ws_off;
 }
 
-// Members of dispatch d in launch order.
-std::vector<int> dispatch_members(const gdy_plan_t& p, int d) {
-  std::vector<int> out;
-  for (int t = 0; t < GDY_MAX_GEMMS && p.order[t] >= 0; ++t)
-    if (p.dispatch_of[p.order[t]] == d) out.push_back(p.order[t]);
-  return out;
-}
-
 // One kernel launch: a dispatch, or several dispatches of a group (each GEMM
 // on the kernel the plan names) run jointly in one grid.
 struct Unit {
-  std::vector<int> ids;      // its dispatches
-  std::vector<int> members;  // their GEMMs and adds, launch order
-  int joint = 0;             // its family, 0: one dispatch on its own kernel
+  int group;
+  int dispatch;      // its first dispatch
+  int first, count;  // its members in Launches::member
+  int joint;         // its family, 0: one dispatch on its own kernel
+};
+
+// The launches of a plan, its groups one after another.  Planned once a call;
+// in fixed arrays, as a small submission is bound by the host.
+struct Launches {
+  int n = 0, members_n = 0;
+  Unit unit[GDY_MAX_GEMMS];
+  int member[GDY_MAX_GEMMS];  // of each unit, launch order
+  Members of(const Unit& x) const { return Members(member + x.first, x.count); }
+  void add(int group, int dispatch, const Members& m, int joint) {
+    unit[n++] = Unit{group, dispatch, members_n, m.size(), joint};
+    for (int i : m) member[members_n++] = i;
+  }
 };
 
 // The modes whose groups run dispatches jointly.  Not under a CU budget: a joint
@@ -1544,9 +1564,52 @@ const double kJoinUs = 40.0;
 const double kSmallTile = 0.32;  // a 128 x 128 tile's share of a CU
 const double kForkSteps = 840;   // a fork and join, 20 us, in steps of K of a 16-bit 256 x 256 tile (23.7 ns)
 const int64_t kWidenK = 1024;    // the shortest K that changes to 256 x 256 tiles
-std::vector<Unit> launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
-                               const std::vector<int>& ids, const std::vector<std::vector<int>>& members) {
-  std::vector<Unit> out;
+// Whether a dispatch of smaller tiles can run on 256 x 256 ones (family 2): 128
+// x 128 tiles, unsplit, of a long K, whose operands take copies.
+bool widenable(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const Members& members) {
+  for (int i : members) {
+    if (is_add_variant(ctx, p.variant_of[i])) continue;
+    const Exec e = exec_of(ctx, p.variant_of[i], g[i]);
+    if (e.family != 1 || e.jbm != 128 || e.jbn != 128 || g[i].a_type == DT_F32 || p.split_of[i] > 1 ||
+        g[i].k < kWidenK || !a_copies(g[i]) || !b_copies(g[i]) || ctx->variants[p.variant_of[i]].cap > 0)
+      return false;
+  }
+  return true;
+}
+
+// The estimate on 256 x 256 tiles, of 256 or 128 rows.
+double wide_estimate(const gdy_ctx* ctx, const gdy_gemm* g, const Members& members) {
+  return std::min(launch_estimate(ctx->cus, g, members, 256, 256, 1.0, 1.0),
+                  launch_estimate(ctx->cus, g, members, 128, 256, kHalfTile, kHalfTile));
+}
+
+// The members of the last unit, if it is joint: the longest work items first, as
+// within a dispatch; adds last.
+void order_joint(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, Launches* out) {
+  const Unit& x = out->unit[out->n - 1];
+  if (!x.joint) return;
+  auto item = [&](int i) {
+    const Exec e = joint_exec(ctx, p.variant_of[i], g[i], x.joint);
+    return g[i].k / std::max(p.split_of[i], 1) * e.jbm * e.jbn;
+  };
+  std::stable_sort(out->member + x.first, out->member + x.first + x.count, [&](int a, int b) {
+    const bool ea = g[a].op == GDY_OP_ADD, eb = g[b].op == GDY_OP_ADD;
+    return ea || eb ? !ea && eb : item(a) > item(b);
+  });
+}
+
+// A group of one dispatch: one launch, on 256 x 256 tiles where that wins.
+void launch_lone(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode, int group,
+                 const Members& members, Launches* out) {
+  const bool wide = joint_mode(ctx, mode) && widenable(ctx, g, p, members) &&
+                    wide_estimate(ctx, g, members) <
+                        0.9 * launch_estimate(ctx->cus, g, members, 128, 128, 2 * kSmallTile, kSmallTile);
+  out->add(group, p.dispatch_of[members[0]], members, wide ? 2 : 0);
+  order_joint(ctx, g, p, out);
+}
+
+void launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode, int group,
+                  const std::vector<int>& ids, const std::vector<std::vector<int>>& members, Launches* out) {
   std::vector<int> family(ids.size(), 0), dtype(ids.size(), 0);
   double large_s = 0.0;
   for (size_t u = 0; u < ids.size(); ++u) {
@@ -1572,104 +1635,83 @@ std::vector<Unit> launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_
   // 256 x 256 ones 218.  Short K is left alone: the estimate knows no prologue
   // and no store.
   for (size_t u = 0; u < ids.size(); ++u) {
-    if (family[u] != 1 || dtype[u] == DT_F32) continue;
+    if (family[u] != 1 || !widenable(ctx, g, p, members[u])) continue;
     std::vector<int> small, large, all;
     bool fits = true;
     for (size_t q = 0; q < ids.size(); ++q) {
       if (family[q] == 0 || dtype[q] != dtype[u]) continue;
-      for (int i : members[q]) {
-        (family[q] == 1 ? small : large).push_back(i);
-        all.push_back(i);
-        if (family[q] != 1 || is_add_variant(ctx, p.variant_of[i])) continue;
-        const Exec e = exec_of(ctx, p.variant_of[i], g[i]);
-        fits = fits && e.jbm == 128 && e.jbn == 128 && p.split_of[i] <= 1 && g[i].k >= kWidenK && a_copies(g[i]) &&
-               b_copies(g[i]);
-      }
+      fits = fits && (family[q] != 1 || widenable(ctx, g, p, members[q]));
+      std::vector<int>& part = family[q] == 1 ? small : large;
+      part.insert(part.end(), members[q].begin(), members[q].end());
+      all.insert(all.end(), members[q].begin(), members[q].end());
     }
-    auto wide = [&](const std::vector<int>& m) {
-      return std::min(launch_estimate(ctx->cus, g, m, 256, 256, 1.0, 1.0),
-                      launch_estimate(ctx->cus, g, m, 128, 256, kHalfTile, kHalfTile));
-    };
-    fits = fits && (int)all.size() <= kMaxFused;
+    if (!fits || (int)all.size() > kMaxFused) continue;
     double apart = launch_estimate(ctx->cus, g, small, 128, 128, 2 * kSmallTile, kSmallTile);
-    if (!large.empty()) apart += wide(large) + (dtype[u] == DT_FP8 ? 2 : 1) * kForkSteps;
-    if (fits && wide(all) < 0.9 * apart)
+    if (!large.empty()) apart += wide_estimate(ctx, g, large) + (dtype[u] == DT_FP8 ? 2 : 1) * kForkSteps;
+    if (wide_estimate(ctx, g, all) < 0.9 * apart)
       for (size_t q = 0; q < ids.size(); ++q)
         if (family[q] == 1 && dtype[q] == dtype[u]) family[q] = 2;
   }
-  std::vector<size_t> first;  // the dispatch that opened each launch
+  std::vector<char> done(ids.size(), 0);
   for (size_t u = 0; u < ids.size(); ++u) {
-    size_t q = 0;
-    while (q < out.size() && !(family[u] > 0 && family[first[q]] == family[u] && dtype[first[q]] == dtype[u] &&
-                               out[q].members.size() + members[u].size() <= (size_t)kMaxFused))
-      ++q;
-    if (q == out.size()) {
-      out.emplace_back();
-      first.push_back(u);
-    } else {
-      out[q].joint = family[u];
+    if (done[u]) continue;
+    std::vector<int> all = members[u];
+    bool joint = false;
+    // the later dispatches of its family and type, as long as there is room
+    for (size_t q = u + 1; q < ids.size() && family[u] > 0; ++q) {
+      if (done[q] || family[q] != family[u] || dtype[q] != dtype[u] ||
+          all.size() + members[q].size() > (size_t)kMaxFused)
+        continue;
+      done[q] = 1;
+      joint = true;
+      all.insert(all.end(), members[q].begin(), members[q].end());
     }
-    out[q].ids.push_back(ids[u]);
-    out[q].members.insert(out[q].members.end(), members[u].begin(), members[u].end());
-  }
-  // a launch of one dispatch runs jointly where that changes its tiles
-  for (size_t q = 0; q < out.size(); ++q) {
-    const size_t u = first[q];
-    if (out[q].joint || family[u] == 0) continue;
-    for (int i : out[q].members) {
-      if (is_add_variant(ctx, p.variant_of[i])) continue;
-      const Exec e = exec_of(ctx, p.variant_of[i], g[i]);
-      if (e.family != family[u]) out[q].joint = family[u];
-    }
-  }
-  // the longest work items first, as within a dispatch; adds last
-  for (Unit& x : out)
-    if (x.joint) {
-      auto item = [&](int i) {
-        const Exec e = joint_exec(ctx, p.variant_of[i], g[i], x.joint);
-        return g[i].k / std::max(p.split_of[i], 1) * e.jbm * e.jbn;
-      };
-      std::stable_sort(x.members.begin(), x.members.end(), [&](int a, int b) {
-        const bool ea = g[a].op == GDY_OP_ADD, eb = g[b].op == GDY_OP_ADD;
-        return ea || eb ? !ea && eb : item(a) > item(b);
-      });
-    }
-  return out;
-}
-
-// The dispatches of group grp (launch order) and their members.
-void group_dispatches(const gdy_plan_t& p, int grp, std::vector<int>* ids, std::vector<std::vector<int>>* members) {
-  for (int t = 0; t < GDY_MAX_GEMMS && p.order[t] >= 0; ++t) {
-    const int i = p.order[t];
-    if (p.group_of[i] != grp) continue;
-    size_t u = 0;
-    while (u < ids->size() && (*ids)[u] != p.dispatch_of[i]) ++u;
-    if (u == ids->size()) {
-      ids->push_back(p.dispatch_of[i]);
-      members->emplace_back();
-    }
-    (*members)[u].push_back(i);
+    // a launch of one dispatch runs jointly where that changes its tiles
+    if (!joint && family[u] > 0)
+      for (int i : all)
+        if (!is_add_variant(ctx, p.variant_of[i]) && exec_of(ctx, p.variant_of[i], g[i]).family != family[u]) joint = true;
+    out->add(group, ids[u], all, joint ? family[u] : 0);
+    order_joint(ctx, g, p, out);
   }
 }
 
-// Streams of the joint modes' launches: a group's first launch on the origin
-// stream, the others round-robin on the pool.
-void plan_units(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode) {
-  if (!joint_mode(ctx, mode) || p->n_dispatches <= p->n_groups) return;
+// The launches of a plan, and the streams of the joint modes': a group's first
+// launch on the origin stream, the others round-robin on the pool.
+void plan_units(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode, Launches* out) {
   const int S = std::max(pool_size(ctx), 1);
+  int t = 0;  // groups are contiguous in launch order
   for (int grp = 0; grp < p->n_groups; ++grp) {
+    const int t0 = t;
+    bool lone = true;
+    for (; t < GDY_MAX_GEMMS && p->order[t] >= 0 && p->group_of[p->order[t]] == grp; ++t)
+      lone = lone && p->dispatch_of[p->order[t]] == p->dispatch_of[p->order[t0]];
+    if (t == t0) continue;
+    if (lone) {
+      launch_lone(ctx, g, *p, mode, grp, Members(p->order + t0, t - t0), out);
+      continue;
+    }
     std::vector<int> ids;
     std::vector<std::vector<int>> members;
-    group_dispatches(*p, grp, &ids, &members);
-    if (ids.size() < 2) continue;
-    const std::vector<Unit> units = launch_units(ctx, g, *p, mode, ids, members);
-    for (size_t u = 0; u < units.size(); ++u)
-      for (int i : units[u].members) p->stream_of[i] = u == 0 ? -1 : (int)(u - 1) % S;
+    for (int x = t0; x < t; ++x) {
+      const int i = p->order[x];
+      size_t u = 0;
+      while (u < ids.size() && ids[u] != p->dispatch_of[i]) ++u;
+      if (u == ids.size()) {
+        ids.push_back(p->dispatch_of[i]);
+        members.emplace_back();
+      }
+      members[u].push_back(i);
+    }
+    const int first = out->n;
+    launch_units(ctx, g, *p, mode, grp, ids, members, out);
+    if (!joint_mode(ctx, mode)) continue;
+    for (int u = first; u < out->n; ++u)
+      for (int i : out->of(out->unit[u])) p->stream_of[i] = u == first ? -1 : (u - first - 1) % S;
   }
 }
 
 gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode,
-                       hipStream_t origin, float* ws_base, int64_t ws_cap) {
+                       const Launches& launches, hipStream_t origin, float* ws_base, int64_t ws_cap) {
   gdy_status st = GDY_OK;
   const int n = p.n;
   // stream slots: the pool (or the active CU budget's pool), or the CU
@@ -1700,14 +1742,12 @@ gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
     HIP_TRY(ctx, hipEventRecord(ts->sub_start, origin));
   }
 
-  for (int grp = 0; grp < p.n_groups && st == GDY_OK; ++grp) {
-    std::vector<int> ids;
-    std::vector<std::vector<int>> members;
-    group_dispatches(p, grp, &ids, &members);
-    const std::vector<Unit> units = launch_units(ctx, g, p, mode, ids, members);
+  // a group's launches: unit[first], ..., unit[end - 1]
+  for (int first = 0, end = 0; first < launches.n && st == GDY_OK; first = end) {
+    while (end < launches.n && launches.unit[end].group == launches.unit[first].group) ++end;
     std::vector<int> slots;  // pool slots the group uses
-    for (const Unit& x : units) {
-      const int s = p.stream_of[x.members[0]];
+    for (int q = first; q < end; ++q) {
+      const int s = p.stream_of[launches.of(launches.unit[q])[0]];
       if (s >= 0 && std::find(slots.begin(), slots.end(), s) == slots.end()) slots.push_back(s);
     }
     // fork: pool streams start after what the origin holds
@@ -1715,9 +1755,11 @@ gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
       HIP_TRY(ctx, hipEventRecord(ctx->fork_ev, origin));
       for (int s : slots) HIP_TRY(ctx, hipStreamWaitEvent(stream_at(s), ctx->fork_ev, 0));
     }
-    for (const Unit& x : units) {
-      int i0 = x.members[0];  // the launch runs its first GEMM's kernel (adds ride along)
-      for (int i : x.members)
+    for (int q = first; q < end; ++q) {
+      const Unit& x = launches.unit[q];
+      const Members members = launches.of(x);
+      int i0 = members[0];  // the launch runs its first GEMM's kernel (adds ride along)
+      for (int i : members)
         if (!is_add_variant(ctx, p.variant_of[i])) {
           i0 = i;
           break;
@@ -1727,10 +1769,10 @@ gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
       KLaunch launch;
       int grid = 0;
       bool split = false;
-      st = build_launch(ctx, g, p, mode, x.members, x.joint, ws_off, ws_base, ws_cap, &launch, &grid, &split);
+      st = build_launch(ctx, g, p, mode, members, x.joint, ws_off, ws_base, ws_cap, &launch, &grid, &split);
       if (st != GDY_OK) break;
       void* argv[] = {&launch};
-      const int d = x.ids[0];
+      const int d = x.dispatch;
       const void* func = x.joint ? joint_kernel(g[i0].a_type, x.joint) : split ? ex.func_split : ex.func;
       const int waves = !x.joint ? ex.waves : x.joint == 1 ? 4 : 8;
       hipStream_t hs = p.stream_of[i0] >= 0 ? stream_at(p.stream_of[i0]) : origin;
@@ -1740,19 +1782,19 @@ gdy_status launch_plan(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int
         // the split members' planes summed into C, on the same stream
         KLaunch red;
         int rgrid = 0;
-        build_reduce(ctx, g, p, x.members, launch, &red, &rgrid);
+        build_reduce(ctx, g, p, members, launch, &red, &rgrid);
         void* rargv[] = {&red};
         e = hipExtLaunchKernel(split_reduce_kernel(g[i0].c_type), dim3(rgrid), dim3(256), rargv, 0, hs, nullptr,
                                ts ? ts->stop[d] : nullptr, 0);
       }
       if (e != hipSuccess) {
         st = fail(ctx, GDY_ERR_HIP, "launch of %s (%d GEMMs, first %d) failed: %s",
-                  ctx->variants[vid].name.c_str(), (int)x.members.size(), i0, hipGetErrorString(e));
+                  ctx->variants[vid].name.c_str(), members.size(), i0, hipGetErrorString(e));
         break;
       }
       if (ts) {  // the dispatches of a joint launch report its interval
         ts->launched[d] = 1;
-        for (int i : x.members) ts->dispatch_of[i] = d;
+        for (int i : members) ts->dispatch_of[i] = d;
       }
     }
     // join: the origin continues after the group's pool streams
@@ -2221,8 +2263,8 @@ gdy_status gdy_set_rc(gdy_ctx* ctx, int32_t budget_cus) {
   return fail(ctx, GDY_ERR_INVALID_ARG, "no CU-masked pool for %d CUs", budget_cus);
 }
 
-gdy_status gdy_plan(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int32_t mode, int32_t forced_cd,
-                    gdy_plan_t* out) {
+static gdy_status plan_impl(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int32_t mode, int32_t forced_cd,
+                            gdy_plan_t* out, Launches* launches) {
   if (!ctx || !out) return GDY_ERR_INVALID_ARG;
   ctx->err.clear();
   try {
@@ -2230,7 +2272,7 @@ gdy_status gdy_plan(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int32_t mode
     if (s != GDY_OK) return s;
     if (partition_mode(mode) && forced_cd != 0 && forced_cd != 2 && forced_cd != 4 && forced_cd != 8)
       return fail(ctx, GDY_ERR_INVALID_ARG, "CU-Partition takes 2, 4 or 8 partitions, not %d", forced_cd);
-    make_plan(ctx, gemms, n, mode, forced_cd, out);
+    make_plan(ctx, gemms, n, mode, forced_cd, out, launches);
   } catch (...) {
     return fail(ctx, GDY_ERR_NOMEM, "host allocation failed");
   }
@@ -2240,12 +2282,19 @@ gdy_status gdy_plan(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int32_t mode
   return GDY_OK;
 }
 
+gdy_status gdy_plan(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int32_t mode, int32_t forced_cd,
+                    gdy_plan_t* out) {
+  Launches launches;
+  return plan_impl(ctx, gemms, n, mode, forced_cd, out, &launches);
+}
+
 static gdy_status execute_impl(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int32_t mode, int32_t forced_cd,
                                void* hip_stream, gdy_plan_t* out, bool use_static) {
   if (!ctx) return GDY_ERR_INVALID_ARG;
   gdy_plan_t local;
   gdy_plan_t* p = out ? out : &local;
-  gdy_status s = gdy_plan(ctx, gemms, n, mode, forced_cd, p);
+  Launches launches;
+  gdy_status s = plan_impl(ctx, gemms, n, mode, forced_cd, p, &launches);
   if (s != GDY_OK) return s;
   if (ctx->device < 0) return fail(ctx, GDY_ERR_UNSUPPORTED, "host-only context cannot execute");
   float* ws = ctx->split_ws;
@@ -2262,7 +2311,7 @@ static gdy_status execute_impl(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, i
   int cur = -1;
   if (hipGetDevice(&cur) != hipSuccess || cur != ctx->device) HIP_TRY(ctx, hipSetDevice(ctx->device));
   try {
-    return launch_plan(ctx, gemms, *p, mode, (hipStream_t)hip_stream, ws, cap);
+    return launch_plan(ctx, gemms, *p, mode, launches, (hipStream_t)hip_stream, ws, cap);
   } catch (...) {
     return fail(ctx, GDY_ERR_NOMEM, "host allocation failed");
   }
@@ -2284,22 +2333,23 @@ gdy_status gdy_dispatch_map(gdy_ctx* ctx, const gdy_gemm* gemms, int32_t n, int3
   if (!ctx || !grid || (max_workgroups > 0 && (!gemm_of_wg || !first_item || !item_stride)) || !items_of_gemm)
     return GDY_ERR_INVALID_ARG;
   gdy_plan_t p;
-  gdy_status s = gdy_plan(ctx, gemms, n, mode, forced_cd, &p);
+  Launches launches;
+  gdy_status s = plan_impl(ctx, gemms, n, mode, forced_cd, &p, &launches);
   if (s != GDY_OK) return s;
   if (dispatch < 0 || dispatch >= p.n_dispatches) return fail(ctx, GDY_ERR_INVALID_ARG, "no dispatch %d", dispatch);
   try {
     // the launch that holds the dispatch; workgroups of its other dispatches
     // count as idle
-    std::vector<int> members = dispatch_members(p, dispatch);
-    std::vector<int> ids;
-    std::vector<std::vector<int>> of;
-    group_dispatches(p, p.group_of[members[0]], &ids, &of);
-    int joint = 0;
-    for (const Unit& x : launch_units(ctx, gemms, p, mode, ids, of))
-      if (std::find(x.ids.begin(), x.ids.end(), dispatch) != x.ids.end()) {
-        members = x.members;
-        joint = x.joint;
-      }
+    int u0 = 0;
+    auto holds = [&](const Unit& x) {
+      for (int i : launches.of(x))
+        if (p.dispatch_of[i] == dispatch) return true;
+      return false;
+    };
+    while (u0 < launches.n && !holds(launches.unit[u0])) ++u0;
+    if (u0 == launches.n) return fail(ctx, GDY_ERR_INVALID_ARG, "no dispatch %d", dispatch);
+    const Members members = launches.of(launches.unit[u0]);
+    const int joint = launches.unit[u0].joint;
     const std::vector<int64_t> ws_off = ws_offsets(gemms, p, mode);
     KLaunch L;
     int g = 0;
