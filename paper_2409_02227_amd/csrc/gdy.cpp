@@ -1561,7 +1561,9 @@ bool joint_mode(const gdy_ctx* ctx, int mode) {
 // quarter longer (4096^3 bf16: 124 us, 100 on 256 x 256), a fork and join
 // 20-25 us, so below kJoinUs of roofline time they join.
 const double kJoinUs = 40.0;
-const double kSmallTile = 0.32;  // a 128 x 128 tile's share of a CU
+const double kSmallTile = 0.32;  // a 128 x 128 tile's share of a CU that holds two of them
+const double kLoneTile = 0.42;   // one whose stages take the CU's LDS alone (four of them)
+const double kMidTile = 0.72;    // a 256 x 128 or 128 x 256 tile, in its own kernel
 const double kForkSteps = 840;   // a fork and join, 20 us, in steps of K of a 16-bit 256 x 256 tile (23.7 ns)
 const int64_t kWidenK = 1024;    // the shortest K that changes to 256 x 256 tiles
 // Whether a dispatch of smaller tiles can run on 256 x 256 ones (family 2): 128
@@ -1583,6 +1585,24 @@ double wide_estimate(const gdy_ctx* ctx, const gdy_gemm* g, const Members& membe
                   launch_estimate(ctx->cus, g, members, 128, 256, kHalfTile, kHalfTile));
 }
 
+// The estimate of dispatches of 128 x 128 and larger tiles, not widened:
+// jointly all run 128 x 128 tiles, two to a CU; a lone dispatch runs its own
+// kernel's tiles, of which a CU holds one where they are larger or have four
+// stages (4096^3 bf16, in tiles of a 256 x 256 launch of 97 us: 256 x 128 ones
+// 135 us, 128 x 256 ones 143, 128 x 128 ones of four stages 161, of two 124).
+// Priced as 128 x 128 tiles, (512, 12288, 6144) stayed on 256 x 128 ones.
+double small_estimate(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, const Members& members, bool lone) {
+  for (int i : members) {
+    if (!lone || is_add_variant(ctx, p.variant_of[i])) continue;
+    const KernelDesc* d = ctx->kernels[ctx->variants[p.variant_of[i]].kernel].d;
+    const double item = d->bm * d->bn > 128 * 128 ? kMidTile : kLoneTile;
+    if (d->bm * d->bn > 128 * 128 || d->lds_bytes > 80 * 1024)
+      return launch_estimate(ctx->cus, g, members, d->bm, d->bn, item, item);
+    break;
+  }
+  return launch_estimate(ctx->cus, g, members, 128, 128, 2 * kSmallTile, kSmallTile);
+}
+
 // The members of the last unit, if it is joint: the longest work items first, as
 // within a dispatch; adds last.
 void order_joint(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, Launches* out) {
@@ -1602,8 +1622,7 @@ void order_joint(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, Lau
 void launch_lone(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, int mode, int group,
                  const Members& members, Launches* out) {
   const bool wide = joint_mode(ctx, mode) && widenable(ctx, g, p, members) &&
-                    wide_estimate(ctx, g, members) <
-                        0.9 * launch_estimate(ctx->cus, g, members, 128, 128, 2 * kSmallTile, kSmallTile);
+                    wide_estimate(ctx, g, members) < 0.9 * small_estimate(ctx, g, p, members, true);
   out->add(group, p.dispatch_of[members[0]], members, wide ? 2 : 0);
   order_joint(ctx, g, p, out);
 }
@@ -1646,7 +1665,7 @@ void launch_units(const gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, in
       all.insert(all.end(), members[q].begin(), members[q].end());
     }
     if (!fits || (int)all.size() > kMaxFused) continue;
-    double apart = launch_estimate(ctx->cus, g, small, 128, 128, 2 * kSmallTile, kSmallTile);
+    double apart = small_estimate(ctx, g, p, small, small.size() == members[u].size());
     if (!large.empty()) apart += wide_estimate(ctx, g, large) + (dtype[u] == DT_FP8 ? 2 : 1) * kForkSteps;
     if (wide_estimate(ctx, g, all) < 0.9 * apart)
       for (size_t q = 0; q < ids.size(); ++q)

@@ -172,3 +172,26 @@ def test_half_rows_count_the_cus_of_the_stream(tmp_path):
             assert [ctx.variant(v)["name"] for v in p["variant_of"][:4]] == [name] * 4
             for d in range(4):
                 assert ctx.dispatch_map(descs, mode=mode, forced_cd=4, dispatch=d)["grid"] == quarter
+
+
+@pytest.mark.parametrize("kernel,m,k,own,runs", [
+    # (600, 4096, K) on 256 x 128 tiles: 3 x 32 of 0.72 of a 256 x 256 tile's time at once; 128-row halves: 5 x 16 of
+    # 0.6 < 0.9 * 0.72
+    ("256x128_w2x2_d3", 600, 1024, 96, 80),
+    ("256x128_w2x2_d3", 600, 960, 96, 96),      # short K keeps its kernel
+    # (2048, 4096, K) on 128 x 128 tiles of four stages, one to a CU: 512 take 2 * 0.42 + 0.21 = 1.05, 16 x 16 halves 0.6
+    ("128x128_w2x2_d4", 2048, 1024, 512, 256),
+    ("128x128_w2x2_d2", 2048, 1024, 512, 512),  # all 512 resident: 0.64, and 0.6 > 0.9 * 0.64
+    ("128x128_w2x2_d2", 4096, 1024, 1024, 256),  # 0.32 * 4 + 0.32 = 1.6 against 256 whole tiles: 1
+])
+def test_lone_dispatch_is_priced_on_its_own_tiles(tmp_path, kernel, m, k, own, runs):
+    """GO binds one kernel; the launch keeps its tiles or runs 256 x 256 ones,
+    by the estimate of what each would take (256 CUs)."""
+    name = f"bf16_nn_{kernel}_c0"
+    path = tmp_path / "lone.table"
+    path.write_text(f"gdy-go-table 2\ndevice host cus 256\ncatalogue 0\nentry 2 0 0 11 4096 1024 1 {' '.join([name] * 5)}\n")
+    ctx = gdy.Context(-1, table=str(path))
+    d = _desc(m, 4096, k, 2, 0)
+    assert ctx.variant(ctx.plan([d], mode="go")["variant_of"][0])["name"] == name
+    assert ctx.dispatch_map([d], mode="sequential")["grid"] == own
+    assert ctx.dispatch_map([d], mode="go")["grid"] == runs
