@@ -31,9 +31,52 @@ SHAPES = [("nn", 300, 1000, 520, 0), ("nt", 77, 512, 1024, 0), ("nt", 1000, 640,
           ("tn", 513, 515, 1040, 1), ("nn", 260, 260, 64, 0)]
 
 
+# (layout, m, n, k, pad, kernel): every tile of the joint kernel in the layouts that have it, wider tiles that run as
+# those, operands of any alignment, K tails, split K on four tile sizes, and 256 x 256 kernels, which join short
+# groups as 128 x 128 tiles (with operands that take copies and that do not)
+MIXED = [("nn", 300, 1000, 520, 0, "128x128_w2x2_m32"), ("nt", 77, 512, 1024, 0, "64x128_w1x4_m32"),
+         ("nt", 1000, 640, 512, 1, "64x64_w2x2_m32"), ("nn", 16, 1024, 8192, 0, "16x64_w1x4_m16"),
+         ("nn", 40, 1024, 8192, 0, "64x64_w2x2_m32"), ("nt", 33, 257, 8192, 3, "32x128_w1x4_m32"),
+         ("nn", 130, 512, 8192, 0, "128x128_w2x2_m32"), ("nn", 1, 700, 333, 3, "16x256_w1x4_m16"),
+         ("tn", 256, 300, 200, 0, "128x128_w2x2_m32"), ("tt", 130, 128, 384, 8, "64x64_w2x2_m32"),
+         ("tn", 513, 515, 1040, 1, "256x256_w2x4_m32"), ("nn", 260, 260, 64, 0, "64x256_w1x4_m32"),
+         ("nt", 200, 333, 1040, 0, "256x128_w2x2_m32"), ("nn", 90, 640, 512, 0, "32x256_w1x4_m32"),
+         ("tt", 17, 40, 96, 0, "16x64_w1x4_m16"), ("nn", 700, 512, 1024, 0, "256x256_w2x4_m32")]
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16", "fp8", "f32"])
+@pytest.mark.parametrize("order", [1, -1])
+def test_mixed_tiles_in_one_launch(ctx, tmp_path, dt, order):
+    """GO under a table that binds each of 16 GEMMs to a kernel of its own tile
+    and layout: a dispatch per kernel, one launch, each result that of its
+    kernel alone bit for bit and within the oracle's bound."""
+    rows = MIXED[::order]
+    t = gdy.Context(0, table=bound_table(tmp_path / "mixed.table", ctx, [(dt,) + r[:4] for r in rows], [r[5] for r in rows]))
+    try:
+        mats = [inputs.materialize(GemmSpec(m, n, k, dt, int(lay[0] == "t"), int(lay[1] == "t"), seed=9400 + i, pad_a=pad,
+                                            pad_b=pad, name=f"{dt}_{lay}_{m}x{n}x{k}"))
+                for i, (lay, m, n, k, pad, _) in enumerate(rows)]
+        gemms = [gemm_of(m) for m in mats]
+        reset_outputs(mats)
+        plan = t.execute(gemms, mode="go", want_plan=True)
+        torch.cuda.synchronize()
+        assert [t.variant(v)["name"] for v in plan["variant_of"][:16]] == [f"{dt}_{r[0]}_{r[5]}_c0" for r in rows]
+        assert set(plan["stream_of"]) == {-1} and plan["n_dispatches"] == 15  # two members share 128 x 128 nn
+        assert len({t.dispatch_map(gemms, mode="go", dispatch=d)["grid"] for d in range(15)}) == 1
+        split = {r[5].split("_")[0] for r, x in zip(rows, plan["split_of"]) if x > 1}
+        assert split >= {"16x64", "64x64", "32x128", "128x128"}, split
+        for m in mats:
+            check(m, label="joint")
+        same_bits_alone(t, mats, plan)
+    finally:
+        t.close()
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f16", "fp8", "f32"])
 @pytest.mark.parametrize("count", [2, 5, 10])
 def test_bits_and_values(ctx, dt, count):
+    """Groups of dispatches of named kernels (FORCED_GROUPED: one launch each,
+    on pool streams), and the joint GO launch of the isolated heuristics."""
     mats = [inputs.materialize(GemmSpec(m, n, k, dt, int(lay[0] == "t"), int(lay[1] == "t"), seed=9500 + i, pad_a=pad,
                                         pad_b=pad, name=f"{dt}_{lay}_{m}x{n}x{k}"))
             for i, (lay, m, n, k, pad) in enumerate(SHAPES[:count])]
@@ -104,13 +147,15 @@ def test_table_bound_kernels_join(ctx, tmp_path):
 
 
 def bound_table(path, ctx, rows, name):
-    """A GO table that binds each row (dtype code, layout, m, n, k) to the kernel `name` of its type and layout."""
+    """A GO table that binds each row (type, layout, m, n, k) to the kernel `name` of its type and layout (a list: each
+    to its own)."""
+    names = [name] * len(rows) if isinstance(name, str) else name
     lines = ["gdy-go-table 2", f"device gfx950 cus {ctx.cus()}", f"catalogue {ctx.catalogue_hash():016x}"]
     codes = {"f16": 1, "bf16": 2, "fp8": 3, "f32": 4}
-    for dt, lay, m, n, k in rows:
+    for (dt, lay, m, n, k), kernel in zip(rows, names):
         ta, tb = int(lay[0] == "t"), int(lay[1] == "t")
         lines.append(f"entry {codes[dt]} {ta} {tb} {(m - 1).bit_length()} {n} {k} 1 " +
-                     " ".join([f"{dt}_{lay}_{name}_c0"] * 5))
+                     " ".join([f"{dt}_{lay}_{kernel}_c0"] * 5))
     path.write_text("\n".join(lines) + "\n")
     return str(path)
 
@@ -147,11 +192,14 @@ def test_wide_tiles_for_128_row_kernels(ctx, tmp_path, dt, k, layouts):
 
 
 @pytest.mark.parametrize("dt", ["bf16", "fp8"])
-@pytest.mark.parametrize("m,n,k", [(1300, 4096, 1040), (513, 12288, 1040), (2048, 1024, 1040), (1024, 2048, 1040)])
-def test_half_rows(ctx, tmp_path, dt, m, n, k):
+@pytest.mark.parametrize("m,n,half", [(1300, 4096, True), (513, 12288, True), (2048, 1024, True), (1024, 2048, True),
+                                      (3900, 4096, False), (2100, 8192, False), (4096, 4096, False)])
+def test_half_rows(ctx, tmp_path, dt, m, n, half):
     """256 x 256 launches that do not fill the chip cut their tile rows in two
-    (whole, short and one-row last tiles), others do not; the bits are those of
-    the 128 x 128 kernel."""
+    (whole, short and one-row last tiles), others do not: tiles of 256 CUs' worth
+    once (256) or 9 x 32 of them, where halves would take longer.  The bits are
+    those of the 128 x 128 kernel."""
+    k = 1040  # not split on either kernel
     rows = [(dt, "nn", m, n, k)]
     mat = inputs.materialize(GemmSpec(m, n, k, dt, 0, 0, seed=9900 + m, name=f"{dt}_{m}x{n}x{k}"))
     got = {}
@@ -166,11 +214,30 @@ def test_half_rows(ctx, tmp_path, dt, m, n, k):
             got[name] = out_codes(mat).copy()
             assert plan["split_of"][0] == 1
             if name[0] == "2":
-                full, half = -(-m // 256) * -(-n // 256), -(-m // 128) * -(-n // 256)
-                # the estimates at one K: 1 and 0.6 of a tile's time while they fit, else work and half a tile
-                cost = lambda x, t: t if x <= ctx.cus() else t * (x / ctx.cus() + 0.5)  # noqa: E731
-                want = half if cost(half, 0.6) < 0.95 * cost(full, 1.0) else full
-                assert t.dispatch_map([gemm_of(mat)], mode="go")["grid"] == want
+                assert t.dispatch_map([gemm_of(mat)], mode="go")["grid"] == -(-m // (128 if half else 256)) * -(-n // 256)
         finally:
             t.close()
     assert np.array_equal(*got.values())
+
+
+@pytest.mark.parametrize("dt,lay,kernel", [(dt, lay, kernel) for dt, lay in (("bf16", "nn"), ("f16", "nt"), ("fp8", "nn"))
+                                           for kernel in ("256x128_w2x2_m32", "128x256_w2x2_m32", "128x128_w2x2_d4")] +
+                         [("bf16", "tn", "256x128_w2x2_m32")])
+def test_lone_dispatches_on_wide_tiles(ctx, tmp_path, dt, lay, kernel):
+    """A lone dispatch of 256 x 128, 128 x 256 or four-stage 128 x 128 tiles runs
+    on 256 x 256 ones where its own would take longer, with the same bits."""
+    m, n, k = 1990, 3088, 1152
+    t = gdy.Context(0, table=bound_table(tmp_path / "lone.table", ctx, [(dt, lay, m, n, k)], kernel))
+    try:
+        ta, tb = int(lay[0] == "t"), int(lay[1] == "t")
+        mat = inputs.materialize(GemmSpec(m, n, k, dt, ta, tb, seed=9950, pad_a=-(m if ta else k) % 16,
+                                          name=f"{dt}_{lay}_{m}x{n}x{k}"))
+        reset_outputs([mat])
+        plan = t.execute([gemm_of(mat)], mode="go", want_plan=True)
+        torch.cuda.synchronize()
+        assert t.variant(plan["variant_of"][0])["name"] == f"{dt}_{lay}_{kernel}_c0"
+        assert t.dispatch_map([gemm_of(mat)], mode="go")["grid"] == 16 * 13  # 128-row tiles
+        check(mat, label="wide")
+        same_bits_alone(t, [mat], plan)
+    finally:
+        t.close()
