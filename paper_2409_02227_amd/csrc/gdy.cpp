@@ -1179,12 +1179,10 @@ void make_plan_core(const gdy_ctx* ctx, const gdy_gemm* g, int n, int mode, int 
 // ---------------------------------------------------------------------------
 // Launching
 // ---------------------------------------------------------------------------
-// Vector loads need the base, the row pitch and (in a batch) the item
-// stride, all in bytes, aligned to the vector size.
-bool vec_ok(const void* ptr, int64_t ld, int es, bool kcontiguous, int64_t item_stride_bytes) {
-  const uintptr_t a = (uintptr_t)ptr;
-  const int64_t v = (kcontiguous || es >= 2) ? 16 : 8;  // fp8 k-major operand: 8-byte row vectors
-  return a % v == 0 && (ld * es) % v == 0 && item_stride_bytes % v == 0;
+// The add's vector loads need the base, the row pitch and (in a batch) the item
+// stride, all in bytes, aligned to 16 bytes.
+bool vec_ok(const void* ptr, int64_t ld, int es, int64_t item_stride_bytes) {
+  return (uintptr_t)ptr % 16 == 0 && (ld * es) % 16 == 0 && item_stride_bytes % 16 == 0;
 }
 
 // Buffer size for reads: the extent rounded up to the end of the dword that
@@ -1197,8 +1195,7 @@ int32_t read_records(const void* base, int64_t bytes) {
   return (int32_t)(((p + (uintptr_t)bytes + 3) & ~(uintptr_t)3) - p);
 }
 
-KArgs make_args(const gdy_ctx* ctx, int vid, const gdy_gemm& g, Geometry* geo_out) {
-  const Kernel& k = ctx->kernels[ctx->variants[vid].kernel];
+KArgs make_args(const gdy_ctx* ctx, int vid, const gdy_gemm& g) {
   const Geometry geo = geometry(ctx, vid, g);
   const int es = elem_size(g.a_type);
   KArgs a;
@@ -1229,12 +1226,12 @@ KArgs make_args(const gdy_ctx* ctx, int vid, const gdy_gemm& g, Geometry* geo_ou
   a.tiles_m = geo.tiles_m;
   a.tiles_n = geo.tiles_n;
   const bool batched = g.batch > 1;
-  a.a_vec = (g.k > 0 || add) && vec_ok(g.a, g.lda, es, g.trans_a == 0, batched ? g.stride_a * es : 0);
-  a.b_vec = (g.k > 0 || add) && vec_ok(g.b, g.ldb, es, add || g.trans_b == 1, batched ? g.stride_b * es : 0);
+  a.a_vec = add && vec_ok(g.a, g.lda, es, batched ? g.stride_a * es : 0);
+  a.b_vec = add && vec_ok(g.b, g.ldb, es, batched ? g.stride_b * es : 0);
   a.c_vec = (uintptr_t)g.c % 8 == 0 && (g.ldc * out_size(g)) % 8 == 0 &&
             (!batched || (g.stride_c * out_size(g)) % 8 == 0);
-  a.a_dma = a_copies(g);
-  a.b_dma = b_copies(g);
+  a.a_dma = !add && a_copies(g);
+  a.b_dma = !add && b_copies(g);
   a.group_m = 8;
   a.xcd_remap = 1;
   a.batch = (int32_t)std::max(g.batch, 1);
@@ -1243,8 +1240,6 @@ KArgs make_args(const gdy_ctx* ctx, int vid, const gdy_gemm& g, Geometry* geo_ou
   a.stride_a = a.batch > 1 ? g.stride_a * es : 0;
   a.stride_b = a.batch > 1 ? g.stride_b * es : 0;
   a.stride_c = a.batch > 1 ? g.stride_c * out_size(g) : 0;
-  (void)k;
-  if (geo_out) *geo_out = geo;
   return a;
 }
 
@@ -1338,7 +1333,7 @@ gdy_status build_launch(gdy_ctx* ctx, const gdy_gemm* g, const gdy_plan_t& p, in
     const KernelDesc* d = ctx->kernels[v.kernel].d;
     const Exec e = joint ? joint_exec(ctx, p.variant_of[i], g[i], joint) : exec_of(ctx, p.variant_of[i], g[i]);
     KArgs& a = L->g[u];
-    a = make_args(ctx, p.variant_of[i], g[i], nullptr);
+    a = make_args(ctx, p.variant_of[i], g[i]);
     if (!d->ew) {
       const int bm = joint ? e.jbm : e.bm, bn = joint ? e.jbn : e.bn;
       if (tile_m == 0) tile_m = bm, tile_n = bn;

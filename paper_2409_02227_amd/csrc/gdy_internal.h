@@ -25,7 +25,7 @@ struct KArgs {
   int32_t c_bytes;
   int32_t tiles_m;    // ceil(m / BM)
   int32_t tiles_n;    // ceil(n / BN)
-  int32_t a_vec;      // 1: A base and rows are aligned for vector loads
+  int32_t a_vec;      // adds, 1: A base and rows are aligned for vector loads
   int32_t b_vec;      // 1: same for B
   int32_t c_vec;      // 1: C base and rows allow 8-byte stores
   int32_t a_dma;      // 1: A takes direct 16-byte copies to LDS (base, pitch and item stride

@@ -40,8 +40,8 @@ template <int DT> struct OutSize { static constexpr int v = 2; };
 template <> struct OutSize<DT_F32> { static constexpr int v = 4; };
 
 // ---------------------------------------------------------------------------
-// MFMA wrappers.  Frag is one lane's operand fragment (FB bytes of K for one
-// row of A or one column of B); Acc is one lane's share of a 16 x 16 block.
+// MFMA wrappers.  An operand is one lane's fragment (lds_copy.h: FragT); Acc is
+// one lane's share of a 16 x 16 block.
 // Output layout (CDNA matrix-core convention): accumulator r of lane l is row
 // 4*(l/16) + r, column l%16.  Lanes l and l' with l%16 equal hold the same row
 // of A (column of B) at different K offsets; A and B use the same K
@@ -50,19 +50,17 @@ template <> struct OutSize<DT_F32> { static constexpr int v = 4; };
 template <int DT, int MM> struct Mma;
 
 template <> struct Mma<DT_BF16, 16> {
-  typedef u32x4 Frag;
   typedef f32x4 Acc;
-  static constexpr int FB = 16, NACC = 4;
-  static __device__ __forceinline__ Acc run(Frag a, Frag b, Acc c) {
+  static constexpr int NACC = 4;
+  static __device__ __forceinline__ Acc run(u32x4 a, u32x4 b, Acc c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   }
 };
 template <> struct Mma<DT_F16, 16> {
-  typedef u32x4 Frag;
   typedef f32x4 Acc;
-  static constexpr int FB = 16, NACC = 4;
-  static __device__ __forceinline__ Acc run(Frag a, Frag b, Acc c) {
+  static constexpr int NACC = 4;
+  static __device__ __forceinline__ Acc run(u32x4 a, u32x4 b, Acc c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
                                                   __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
   }
@@ -70,20 +68,18 @@ template <> struct Mma<DT_F16, 16> {
 // fp8: the f8f6f4 MFMAs with format 0 (OCP E4M3) for both operands and unit
 // block scales (E8M0 exponent 127 = 2^0).  32 bytes of K per lane.
 template <> struct Mma<DT_FP8, 16> {
-  typedef i32x8 Frag;
   typedef f32x4 Acc;
-  static constexpr int FB = 32, NACC = 4;
-  static __device__ __forceinline__ Acc run(Frag a, Frag b, Acc c) {
+  static constexpr int NACC = 4;
+  static __device__ __forceinline__ Acc run(i32x8 a, i32x8 b, Acc c) {
     return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 127, 0, 127);
   }
 };
 
 // fp32: one element of K per lane.
 template <> struct Mma<DT_F32, 16> {
-  typedef float Frag;
   typedef f32x4 Acc;
-  static constexpr int FB = 4, NACC = 4;
-  static __device__ __forceinline__ Acc run(Frag a, Frag b, Acc c) {
+  static constexpr int NACC = 4;
+  static __device__ __forceinline__ Acc run(float a, float b, Acc c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
 };
