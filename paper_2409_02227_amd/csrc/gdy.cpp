@@ -21,6 +21,7 @@
 #include <mutex>
 #include <sstream>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "gdy.h"
@@ -1858,6 +1859,12 @@ void borrow_entries(const gdy_ctx* ctx, Table* t) {
         const std::vector<int>* from = &t->by_layout[other][ta][tb];
         if (from->empty()) from = &t->by_layout[dt][0][0];
         if (from->empty() && other) from = &t->by_layout[other][0][0];
+        std::vector<int> stands(ctx->variants.size(), -2);  // sibling of each variant here, -2: not looked up
+        auto sibling = [&](int v) {
+          if (v < 0) return -1;
+          if (stands[v] == -2) stands[v] = sibling_variant(ctx, v, dt, ta, tb);
+          return stands[v];
+        };
         for (int i : *from) {
           TableEntry e = t->entries[i];
           e.borrowed = true;
@@ -1865,8 +1872,8 @@ void borrow_entries(const gdy_ctx* ctx, Table* t) {
           e.ta = ta;
           e.tb = tb;
           bool ok = true;
-          for (int& v : e.v) ok = (v = sibling_variant(ctx, v, dt, ta, tb)) >= 0 && ok;
-          for (int& v : e.rc) v = sibling_variant(ctx, v, dt, ta, tb);
+          for (int& v : e.v) ok = (v = sibling(v)) >= 0 && ok;
+          for (int& v : e.rc) v = sibling(v);
           if (ok) add.push_back(e);
         }
       }
@@ -1888,6 +1895,8 @@ gdy_status load_table(gdy_ctx* ctx, const char* path) {
   int have[5][4] = {};  // min, max, w, b seen per block
   bool header = false;
   int version = 0;
+  std::unordered_map<std::string, int> ids;
+  for (size_t v = 0; v < ctx->variants.size(); ++v) ids[ctx->variants[v].name] = (int)v;
   while (std::getline(f, line)) {
     if (line.empty() || line[0] == '#') continue;
     std::istringstream in(line);
@@ -1937,10 +1946,9 @@ gdy_status load_table(gdy_ctx* ctx, const char* path) {
       for (int c = 0; c < GDY_N_CD; ++c) {
         std::string name;
         in >> name;
-        int vid = -1;
-        for (size_t v = 0; v < ctx->variants.size(); ++v)
-          if (ctx->variants[v].name == name) vid = (int)v;
-        if (vid < 0) return fail(ctx, GDY_ERR_TABLE, "GO table names unknown variant %s", name.c_str());
+        const auto found = ids.find(name);
+        if (found == ids.end()) return fail(ctx, GDY_ERR_TABLE, "GO table names unknown variant %s", name.c_str());
+        const int vid = found->second;
         const KernelDesc* d = ctx->kernels[ctx->variants[vid].kernel].d;
         if (d->ew || d->dtype != e.dtype || d->ta != e.ta || d->tb != e.tb)
           return fail(ctx, GDY_ERR_TABLE, "variant %s does not match its entry", name.c_str());
@@ -1949,10 +1957,9 @@ gdy_status load_table(gdy_ctx* ctx, const char* path) {
       // optional: the best kernels under 128, 64 and 32 CUs (CU partitions)
       std::string rname;
       for (int r = 0; r < 3 && (in >> rname); ++r) {
-        int vid = -1;
-        for (size_t v = 0; v < ctx->variants.size(); ++v)
-          if (ctx->variants[v].name == rname) vid = (int)v;
-        if (vid < 0) return fail(ctx, GDY_ERR_TABLE, "GO table names unknown variant %s", rname.c_str());
+        const auto found = ids.find(rname);
+        if (found == ids.end()) return fail(ctx, GDY_ERR_TABLE, "GO table names unknown variant %s", rname.c_str());
+        const int vid = found->second;
         const KernelDesc* d = ctx->kernels[ctx->variants[vid].kernel].d;
         if (d->ew || d->dtype != e.dtype || d->ta != e.ta || d->tb != e.tb)
           return fail(ctx, GDY_ERR_TABLE, "variant %s does not match its entry", rname.c_str());
