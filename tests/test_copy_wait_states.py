@@ -2,7 +2,9 @@
 inserts no wait states: on every path to a copy, five of them lie between it
 and a vector instruction that wrote a scalar register of its descriptor, and
 one between it and a write of M0; and its descriptor must be in scalar
-registers at all.  Read from the built kernels' own code."""
+registers at all.  Rings of several stages count the copies in flight, so their
+kernels may issue no other vector memory instruction in the loop: they use no
+scratch memory.  Read from the built kernels' own code."""
 import os
 import re
 import shutil
@@ -89,7 +91,7 @@ def check_copies(text):
                                   for family in ("d_", "", "joint_") if (family, dt) != ("d_", "f32")])
 def test_wait_states_before_copies(tmp_path, unit):
     obj = os.path.join(BUILD, unit + ".o")
-    tools = [os.path.join(LLVM, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-objdump")]
+    tools = [os.path.join(LLVM, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-objdump", "llvm-readelf")]
     if not os.path.exists(obj) or not all(shutil.which(t) for t in tools):
         pytest.skip("no built kernel objects or LLVM tools")
     fat, dev = str(tmp_path / "fat"), str(tmp_path / "dev.o")
@@ -98,6 +100,10 @@ def test_wait_states_before_copies(tmp_path, unit):
                     "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
     text = subprocess.run([tools[2], "-d", "--no-show-raw-insn", dev], check=True, capture_output=True, text=True).stdout
     assert check_copies(text) > 50
+    if unit.startswith(("kernels_d_", "kernels_joint_")):  # the others have two stages and wait for every copy
+        notes = subprocess.run([tools[3], "--notes", dev], check=True, capture_output=True, text=True).stdout
+        scratch = [int(x) for x in re.findall(r"\.private_segment_fixed_size:\s*(\d+)", notes)]
+        assert len(scratch) > 0 and set(scratch) == {0}, (unit, scratch)
 
 
 COPY_LINE = "buffer_load_dwordx4 v1, s[4:7], 0 offen lds"
