@@ -346,8 +346,8 @@ __device__ __forceinline__ void u_tiles(const KArgs& args, int lwg, int nwg, lds
     if constexpr (SPLIT) {
       if (nsplit > 1) {  // the run's unscaled fp32 partial into its plane
         float* P = split_plane(p, item, s_run);
-        // (not in a joint kernel, which has no registers left for it)
-        constexpr bool ROWS = BM >= 64 && !JOINT;
+        // (direct kernels: the others would lose a resident workgroup to its registers)
+        constexpr bool ROWS = BM >= 64 && !ANY;
         bool whole_rows = false;
         if constexpr (ROWS) whole_rows = (Ncols & 3) == 0;
         if (whole_rows) {

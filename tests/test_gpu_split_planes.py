@@ -1,4 +1,4 @@
-"""Split-K planes of kernels of 64 and more rows leave through LDS, 64 rows at a
+"""Split-K planes of direct kernels of 64 and more rows leave through LDS, 64 rows at a
 time (csrc/go_kernel_u.h): rows that end inside a half of 64, at its edge and one
 past it, columns that end inside a tile, N that is no multiple of four (stored
 from the accumulators), batches, and members of one dispatch with different runs.
@@ -16,8 +16,8 @@ from tests.gpu_helpers import check, gemm_of, reset_outputs  # noqa: E402
 pytestmark = pytest.mark.gpu
 
 KERNELS = [("bf16", "nn", "64x64_w2x2_d4"), ("bf16", "nt", "64x128_w2x2_d4"), ("f16", "nn", "64x256_w1x4_d3"),
-           ("bf16", "tn", "128x128_w2x2_d2"), ("fp8", "nt", "128x128_w2x2_d4"), ("fp8", "nn", "64x128_w1x4_m32"),
-           ("f32", "nt", "128x128_w2x2_m32"), ("f32", "nn", "64x64_w2x2_m32")]
+           ("bf16", "tn", "128x128_w2x2_d2"), ("fp8", "nt", "128x128_w2x2_d4"), ("fp8", "nn", "64x64_w2x2_d4"),
+           ("fp8", "nn", "64x128_w1x4_m32"), ("f32", "nt", "128x128_w2x2_m32")]  # the last two: from the accumulators
 
 
 @pytest.fixture(scope="module")
