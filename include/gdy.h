@@ -220,7 +220,8 @@ typedef struct gdy_ctx gdy_ctx;
  * type and layout a usable table holds no shape of binds the kernels tuned for
  * a sibling (fp16 and bf16 for each other, else the type's untransposed
  * layout), on its own kernels of the closest tiles; its plans report fallback =
- * 1 too.  With nothing to borrow it runs its isolated heuristic.
+ * 1 too.  With nothing to borrow, and alone where it is a batch or fp32, it
+ * runs its isolated heuristic.
  * `use_cu_masks` is a bit set: bit 0 creates one CU-masked stream for each
  * resource constraint GPU/2, GPU/4 and GPU/8 (isolated runs of the tuner);
  * bit 1 creates the CU-Partition streams (2 + 4 + 8 streams whose masks

@@ -108,3 +108,31 @@ def test_nothing_to_borrow(tmp_path):
     # a group of one tuned and one untuned member reports it too
     p = t.plan([desc("bf16", "nn", 512, 1024, 1024, 0), desc("bf16", "nt", 512, 1024, 1024, 1)], mode="selector")
     assert p["fallback"] == 1
+
+
+def test_isolated_kernels_of_batches_and_fp32(tmp_path):
+    """A lone batch or fp32 GEMM of a borrowed layout runs the isolated heuristic's kernel, a lone 16-bit or fp8 GEMM the
+    borrowed one without its grid cap; in a group all bind the borrowed kernels of its class."""
+    capped = ["64x64_w2x2_m32_c128", "128x128_w2x2_m32_c64"] + ["64x64_w2x2_m32_c32"] * 3
+    h = gdy.Context(-1)
+    for dt in ("f16", "fp8", "f32"):
+        t = table(tmp_path / f"{dt}.table", [(dt, "nn", 512, 1024, 1024)], capped, [c.replace("_c128", "_c0") for c in capped[:3]])
+        one, many = desc(dt, "nt", 512, 1024, 512), desc(dt, "nt", 512, 1024, 512)
+        many.batch, many.stride_a, many.stride_b, many.stride_c = 4, 512 * 512, 1024 * 512, 512 * 1024
+        for d, heuristic in ((one, dt == "f32"), (many, True)):
+            vid = t.isolated_variant(d)
+            for mode in ("sequential", "selector", "default"):
+                p = t.plan([d], mode=mode)
+                assert p["variant_of"][0] == vid and p["fallback"] == 1
+            if heuristic:
+                assert vid == h.isolated_variant(d)
+            else:
+                assert t.variant(vid)["name"] == f"{dt}_nt_64x64_w2x2_m32_c0"
+            pair = [d, desc(dt, "nt", 512, 1024, 512, 1)]
+            pair[1].batch, pair[1].stride_a, pair[1].stride_b, pair[1].stride_c = d.batch, d.stride_a, d.stride_b, d.stride_c
+            p = t.plan(pair, mode="go")
+            assert {t.variant(v)["name"] for v in p["variant_of"][:2]} == {f"{dt}_nt_128x128_w2x2_m32_c64"}
+            assert p["fallback"] == 1
+        # the type's tuned layout keeps its caps and its batches
+        own = desc(dt, "nn", 512, 1024, 512)
+        assert t.variant(t.isolated_variant(own))["name"] == f"{dt}_nn_64x64_w2x2_m32_c128"
