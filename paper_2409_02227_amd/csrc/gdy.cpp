@@ -280,25 +280,31 @@ int nearest_entry(const gdy_ctx* ctx, const gdy_gemm& g) {
   return best;
 }
 
-// Variant for CD class ci given the GEMM's nearest tuned entry (-1: none,
-// then the isolated heuristics).  A borrowed entry binds, but the table holds
-// no tuned shape of the GEMM's type and layout: the plan still says so.  Its
+// The kernel of CD class ci of the GEMM's nearest tuned entry (-1: none, then the
+// isolated heuristics): what the CD predictor's features describe.
+int entry_variant(const gdy_ctx* ctx, const gdy_gemm& g, int entry, int ci) {
+  return entry >= 0 ? runnable(ctx, ctx->table.entries[entry].v[ci], g) : heuristic_variant(ctx, g);
+}
+
+// The variant that runs for CD class ci.  A borrowed entry binds, but the table
+// holds no tuned shape of the GEMM's type and layout: the plan still says so.  Its
 // isolated kernel (class 0) runs without the grid cap of the shape it was tuned
 // for ((512, 4096, 1024) fp16 tt 14.6 us capped, 12.1 not), and does not stand for
 // batches, which the borrowed shapes rarely are, nor for fp32: those run the
-// heuristic's.  Over 660 random
-// GEMMs of borrowed layouts run alone, a borrowed kernel was 1.12 (fp16) and 1.03
-// times (fp8) as fast as the heuristic's, but 0.98 and 0.88 times on batches and 0.85
-// in fp32, at its worst 0.14 ((201, 1001, 503) x 16 tn fp32 202 us, 51); in groups
-// the borrowed kernels win (12 fp32 nt GEMMs 336 us, 613; attention scores of
-// five fp16 buckets 8.2, 19.1).
+// heuristic's.  Over 660 random GEMMs of borrowed layouts run alone, a borrowed
+// kernel was 1.12 (fp16) and 1.03 times (fp8) as fast as the heuristic's, but 0.98
+// and 0.88 times on batches and 0.85 in fp32, at its worst 0.14 ((201, 1001, 503) x
+// 16 tn fp32 202 us, 51); in groups the borrowed kernels win (12 fp32 nt GEMMs 336
+// us, 613; attention scores of five fp16 buckets 8.2, 19.1).
 int bind_entry(const gdy_ctx* ctx, const gdy_gemm& g, int entry, int ci, bool* fallback) {
   if (g.op == GDY_OP_ADD) return heuristic_variant(ctx, g);  // the add kernel of its type
   const bool borrowed = entry >= 0 && ctx->table.entries[entry].borrowed;
   if (fallback && (entry < 0 || borrowed)) *fallback = true;
-  if (entry < 0 || (borrowed && ci == 0 && (g.batch > 1 || g.a_type == GDY_F32))) return heuristic_variant(ctx, g);
-  const int v = ctx->table.entries[entry].v[ci];
-  return runnable(ctx, borrowed && ci == 0 ? ctx->variants[v].uncapped : v, g);
+  if (borrowed && ci == 0) {
+    if (g.batch > 1 || g.a_type == GDY_F32) return heuristic_variant(ctx, g);
+    return runnable(ctx, ctx->variants[ctx->table.entries[entry].v[0]].uncapped, g);
+  }
+  return entry_variant(ctx, g, entry, ci);
 }
 
 int bind_variant(const gdy_ctx* ctx, const gdy_gemm& g, int ci, bool* fallback) {
@@ -433,7 +439,7 @@ void unify_short_group(const gdy_ctx* ctx, const gdy_gemm* g, const std::vector<
   for (int i : grp) {
     if (g[i].op == GDY_OP_ADD) continue;
     // the isolated kernel of g[i]'s nearest tuned shape, borrowed ones too (it is to run in a group)
-    const int iso = entry[i] >= 0 ? runnable(ctx, ctx->table.entries[entry[i]].v[0], g[i]) : heuristic_variant(ctx, g[i]);
+    const int iso = entry_variant(ctx, g[i], entry[i], 0);
     if (iso < 0) continue;
     const int v = ctx->variants[iso].uncapped;
     if (std::find(cand.begin(), cand.end(), v) == cand.end()) cand.push_back(v);
@@ -481,7 +487,7 @@ void features(const gdy_ctx* ctx, const gdy_gemm& g, int entry, double* x) {
   x[1] = (double)g.n;
   x[2] = (double)g.k;
   for (int ci = 0; ci < GDY_N_CD; ++ci) {
-    const int vid = bind_entry(ctx, g, entry, ci, nullptr);
+    const int vid = entry_variant(ctx, g, entry, ci);
     double wgs = 0, occ = 0, waves = 0;
     if (vid >= 0) {
       const Geometry geo = geometry(ctx, vid, g);

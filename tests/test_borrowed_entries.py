@@ -136,3 +136,14 @@ def test_isolated_kernels_of_batches_and_fp32(tmp_path):
         # the type's tuned layout keeps its caps and its batches
         own = desc(dt, "nn", 512, 1024, 512)
         assert t.variant(t.isolated_variant(own))["name"] == f"{dt}_nn_64x64_w2x2_m32_c128"
+
+
+def test_features_describe_the_entry(tmp_path):
+    """The predictor's features are of the borrowed entry's kernels, also where the GEMM alone runs the heuristic's: a
+    group forms as its kernels were tuned to."""
+    t = table(tmp_path / "t.table", [("f32", "nn", 512, 1024, 1024)], ["128x128_w2x2_m32_c0"] + ["64x64_w2x2_m32_c0"] * 4,
+              ["64x64_w2x2_m32_c0"] * 3)
+    d = desc("f32", "nt", 512, 1024, 512)
+    assert t.variant(t.isolated_variant(d))["name"] != "f32_nt_128x128_w2x2_m32_c0"
+    f = t.features(d)
+    assert list(f[:4]) == [512, 1024, 512, 32] and f[6] == 128  # 4 x 8 tiles of 128 x 128, 8 x 16 of 64 x 64
