@@ -170,7 +170,7 @@ typedef struct {
  * has (CUs x occupancy; a grid cap does not count) and whose K is long runs
  * each tile as S work items over consecutive runs of K tiles: S is the
  * largest power of two up to 16 with S x tiles within the slots, at least
- * 16 K tiles per run and at most 16 MiB of fp32 partial planes; kernels with
+ * 16 K tiles per run (32 where the tiles alone are as many as the CUs) and at most 16 MiB of fp32 partial planes; kernels with
  * tiles above 128 x 128 do not split.  S depends only on the GEMM and its
  * kernel -- never on what runs at the same time -- so a variant gives a GEMM
  * the same bits alone and concurrent.  Each run writes an fp32 M x N plane

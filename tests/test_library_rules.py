@@ -61,8 +61,8 @@ def v(ctx, name):
 
 # --------------------------------------------------------------------------
 # split-K: S = largest power of two <= 16 with S x tiles <= CUs x occupancy,
-# at least 16 K tiles per run and S fp32 M x N planes within 16 MiB; tiles
-# above 128 x 128 never split
+# at least 16 K tiles per run (32 where the tiles fill the CUs) and S fp32 M x N
+# planes within 16 MiB; tiles above 128 x 128 never split
 # --------------------------------------------------------------------------
 
 SPLIT_CASES = [
@@ -85,6 +85,11 @@ SPLIT_CASES = [
     ((16, 1024, 8192), K64, 4, 8),
     # 256 x 256 tiles never split
     ((16, 1024, 8192), K256, 0, 1),
+    # (512, 2048, K) on 64x64: 8 x 32 = 256 tiles, one a CU already: S = 2 (512 <= 512) needs 2 x 32 K tiles, K = 4096;
+    # planes 2 x 512 x 2048 x 4 B = 8 MiB.  One tile row less (224 tiles): 2 x 16, K = 2048
+    ((512, 2048, 2048), K64, 0, 1),
+    ((512, 2048, 4096), K64, 0, 2),
+    ((448, 2048, 2048), K64, 0, 2),
 ]
 
 
