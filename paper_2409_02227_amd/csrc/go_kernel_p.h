@@ -10,13 +10,13 @@
 // wave whose operands are in registers, and LDS reads, copy issue and barrier
 // arrival run beside MFMAs instead of between them.
 //
-// What bounds it: with all-zero operands an 8192^3 bf16 GEMM runs at 1870
-// TFLOP/s, with random ones the chip lowers its clock and it runs at 1455, so
-// energy per flop sets the rate of a large GEMM.  That decides the MFMA: 16 x
-// 16 blocks move half the accumulator registers per flop of 32 x 32 ones
-// (8192^3, bf16, B stored N x K: 1445 against 1345 TFLOP/s; the direct loop
-// with one barrier per K tile that this one replaced: 1275; fp8, K x N: 2840,
-// 2770 and 2458).
+// What bounds it: with all-zero operands an 8192^3 bf16 GEMM runs at 1890-1910
+// TFLOP/s, with random ones the chip lowers its clock and it runs at 1445-1515
+// (over chips, layouts and values; fp8 3580-3700 and 2840-2915), so energy per
+// flop sets the rate of a large GEMM.  That decides the MFMA: 16 x 16 blocks move
+// half the accumulator registers per flop of 32 x 32 ones (8192^3, bf16, B stored
+// N x K, one chip: 1445 against 1345 TFLOP/s; the direct loop with one barrier
+// per K tile that this one replaced: 1275; fp8, K x N: 2840, 2770 and 2458).
 //
 // A K tile holds 128 bytes of K per row, as half tiles of 16 KiB: the rows
 // 0-127 and 128-255 of A (A0, A1) and the columns 0-127 and 128-255 of B (B0,

@@ -18,11 +18,13 @@
 // One barrier per K tile.  Direct: S - 1 tiles are in flight while one is
 // computed.  Both ways: tile kt+1 goes to LDS while kt is computed, and in the
 // register way tile kt+2 is being loaded, so a load has a whole tile's time to
-// arrive.  Waves read the fragments of a K step and issue its MFMAs; the other
-// workgroup of the CU fills the gaps (tiles of up to 64 KiB of LDS), which
-// beat prefetching fragments across the barrier within one: 4096^3 bf16 on
-// 128 x 128, two stages, 1107 against 1014 TFLOP/s.  16 x 16 MFMAs (less energy
-// a flop than 32 x 32); the rounded tile leaves through LDS as whole rows.
+// arrive.  Waves read a tile's fragments and issue its MFMAs; the other
+// workgroup of the CU fills the gaps (tiles of up to 64 KiB of LDS).  Prefetching
+// fragments across the barrier is slower, also where a workgroup has the CU to
+// itself: the compiler moves them between the register files ((512, 6144, 12288)
+// bf16 on 128 x 128, four stages, 122 us, 111 without; 4096^3, two stages, 152 and
+// 140).  16 x 16 MFMAs (less energy a flop than 32 x 32); the rounded tile leaves
+// through LDS as whole rows.
 // Unaligned operands, on the kernels with element loads and register
 // transposes before and on these: 2 x (509, 2047, 1021) fp16 on 64 x 64 tiles
 // 55 and 19 us; K tails, 2 x (1000, 2000, 1000) bf16 on 128 x 128: 31 and 18 us.

@@ -42,7 +42,8 @@
   GDY_KERNEL_U(GDY_DT, GDY_DTNAME, TA, TB, L, 16, 128, 1, 4, 16),  \
   GDY_KERNEL_U(GDY_DT, GDY_DTNAME, TA, TB, L, 16, 64, 1, 4, 16)
 
-// Transposed-A layouts carry a smaller set (they are off the timed path).
+// Transposed-A layouts carry a smaller set: weight gradients, which have them, are
+// large in both dimensions and run on the 256 x 256 and 128 x 128 kernels.
 #define GDY_TILES_SMALL(L, TA, TB)                             \
   GDY_KERNEL_256(GDY_DT, GDY_DTNAME, TA, TB, L),                 \
   GDY_KERNEL_LARGE(GDY_DT, GDY_DTNAME, TA, TB, L, 256, 128, 2, 2), \
