@@ -263,16 +263,24 @@ def cpu_model() -> str:
 
 
 def dominant_kernel(ctx, mats, plan, steps, gemms, mode):
-    """Kernel dispatch (a variant over the GEMMs it runs) with the largest
-    total time over the timed steps; returns its name, the GEMMs it covers,
-    per-dispatch algorithmic flops and bytes, and the mean duration from the
-    per-dispatch HIP events (recorded on the stream the dispatch runs on)."""
+    """Kernel launch (a dispatch of one variant over the GEMMs it runs, or the
+    dispatches that share a joint launch, and so report one interval) with
+    the largest total time over the timed steps; returns its first GEMM's
+    variant, the GEMMs it covers, their algorithmic flops and bytes, and the
+    mean duration from the HIP events (recorded on the stream it runs on)."""
     n = len(mats)
     members = {}
     for i in plan["order"]:  # launch order: a dispatch lays its GEMMs out in this order
         d = plan["dispatch_of"][i]
         if d >= 0:
             members.setdefault(d, []).append(i)
+    st, en = ctx.kernel_times(n, 0)
+    launch = {}  # interval -> the first dispatch that reports it
+    for d in list(members):
+        i = members[d][0]
+        first = launch.setdefault((st[i], en[i]), d) if st[i] >= 0 else d
+        if first != d:
+            members[first] += members.pop(d)
     per = {}
     for back in range(min(steps, 64)):
         st, en = ctx.kernel_times(n, back)

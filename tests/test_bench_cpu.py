@@ -64,3 +64,28 @@ def test_every_generator_workload_resolves():
     assert sum(s.flops for s in ls) == 463856467968  # the bench line's flops per step
     assert [s.trans_b for s in inputs.layer_share(trans_b=1)] == [1] * 8
     assert {s.dtype for s in inputs.layer_share(dtype="f32")} == {"f32"}
+
+
+def test_dominant_kernel_counts_a_joint_launch_once():
+    """Dispatches that run in one launch report its interval: the flops of all
+    their GEMMs belong to it."""
+    from types import SimpleNamespace
+
+    specs = [inputs.GemmSpec(512, 1024, 256, "bf16", name=str(i)) for i in range(5)]
+    mats = [SimpleNamespace(spec=s) for s in specs]
+    plan = {"order": [0, 1, 2, 3, 4], "dispatch_of": [0, 0, 1, 2, 3], "variant_of": [7, 7, 8, 9, 9]}
+
+    class Ctx:
+        def kernel_times(self, n, back):  # dispatches 0, 1 and 3 run jointly, 2 beside them and longer
+            return [1.0, 1.0, 1.0, 1.5, 1.0], [3.0 + back, 3.0 + back, 3.0 + back, 3.25, 3.0 + back]
+
+        def variant(self, v):
+            return {"name": f"v{v}"}
+
+        def dispatch_map(self, gemms, mode, dispatch, max_workgroups):
+            return {"grid": 100 + dispatch}
+
+    k = bench.dominant_kernel(Ctx(), mats, plan, 3, None, "go")
+    assert (k["variant"], k["grid"], k["launches"]) == ("v7", 100, 3)
+    assert len(k["shape"]) == 4 and k["flops"] == 4 * 2 * 512 * 1024 * 256
+    assert abs(k["mean_ms"] - 3.0) < 1e-12
