@@ -170,8 +170,10 @@ typedef struct {
  * has (CUs x occupancy; a grid cap does not count) and whose K is long runs
  * each tile as S work items over consecutive runs of K tiles: S is the
  * largest power of two up to 16 with S x tiles within the slots, at least
- * 16 K tiles per run (32 where the tiles alone are as many as the CUs) and at most 16 MiB of fp32 partial planes; kernels with
- * tiles above 128 x 128 do not split.  S depends only on the GEMM and its
+ * 16 K tiles per run (32 in other types than fp32 where the tiles alone are
+ * as many as the CUs) and at most 16 MiB of fp32 partial planes; kernels with
+ * tiles above 128 x 128 do not split.  A GEMM that 16 K tiles a run would
+ * split runs without its variant's grid cap.  S depends only on the GEMM and its
  * kernel -- never on what runs at the same time -- so a variant gives a GEMM
  * the same bits alone and concurrent.  Each run writes an fp32 M x N plane
  * into a workspace the context allocates at creation (256 MiB); a reduction

@@ -823,14 +823,13 @@ int pool_size(const gdy_ctx* ctx) {
 // gives a GEMM the same bits alone and concurrent.  slots = CUs x occupancy
 // (a grid cap does not enter: a split GEMM runs uncapped).  S doubles (up to
 // kMaxSplit) while 2S work items per tile (over every batch item) still fit
-// in the slots, each of the 2S runs keeps kMinSplitKTiles K tiles (twice as
-// many where the tiles give every CU a workgroup already: (1024, 2048, K) bf16 on
-// 64 x 128 tiles, two runs against none, K = 2048 22.2 and 17.0 us, 4096 1.03, 8192
-// 0.88 times), and the 2S fp32 M x N planes fit in kSplitMemberBytes; then S shrinks to the number
-// of runs of ceil(K tiles / S) tiles, so no run is empty.  So a GEMM whose
-// tiles leave most of the GPU idle and whose K is long splits until its runs
-// fill the GPU.
-int split_for(const gdy_ctx* ctx, int vid, const gdy_gemm& g) {
+// in the slots, each of the 2S runs keeps min_run K tiles, and the 2S fp32
+// M x N planes fit in kSplitMemberBytes; then S shrinks to the number of runs
+// of ceil(K tiles / S) tiles, so no run is empty.  So a GEMM whose tiles
+// leave most of the GPU idle and whose K is long splits until its runs fill
+// the GPU.  full_run: K tiles a run where the tiles give every CU a workgroup
+// already.
+int split_count(const gdy_ctx* ctx, int vid, const gdy_gemm& g, int64_t min_run, int64_t full_run) {
   if (vid < 0 || g.op == GDY_OP_ADD || g.k <= 0 || !active(g)) return 1;
   const Variant& v = ctx->variants[vid];
   const Kernel& k = ctx->kernels[v.kernel];
@@ -839,7 +838,7 @@ int split_for(const gdy_ctx* ctx, int vid, const gdy_gemm& g) {
   const int64_t tiles = geometry(ctx, vid, g).tiles;
   const int64_t nk = (g.k + k.d->bk - 1) / k.d->bk;
   const int64_t plane_bytes = (int64_t)g.m * g.n * std::max(g.batch, 1) * 4;
-  const int64_t run = tiles >= ctx->cus ? 2 * kMinSplitKTiles : kMinSplitKTiles;
+  const int64_t run = tiles >= ctx->cus ? full_run : min_run;
   int64_t s = 1;
   while (s * 2 <= kMaxSplit && s * 2 * tiles <= slots && nk >= s * 2 * run &&
          s * 2 * plane_bytes <= kSplitMemberBytes)
@@ -849,6 +848,15 @@ int split_for(const gdy_ctx* ctx, int vid, const gdy_gemm& g) {
     s = (nk + per - 1) / per;
   }
   return (int)s;
+}
+
+// Where every CU has a tile, 16- and 8-bit GEMMs ask for twice kMinSplitKTiles:
+// (1024, 2048, K) bf16 on 64 x 128 tiles, two runs against none, K = 2048 22.2
+// and 17.0 us, 4096 1.03, 8192 0.88 times.  An fp32 K tile takes several times
+// as long and is worth its plane at kMinSplitKTiles: (384, 2048, 1500) nt 39.4
+// split, 45.1 not.
+int split_for(const gdy_ctx* ctx, int vid, const gdy_gemm& g) {
+  return split_count(ctx, vid, g, kMinSplitKTiles, g.a_type == GDY_F32 ? kMinSplitKTiles : 2 * kMinSplitKTiles);
 }
 
 // Workspace bytes of a split GEMM's planes (rounded up to 256).
@@ -879,7 +887,10 @@ int64_t plan_ws_need(const gdy_gemm* g, const gdy_plan_t& p, int mode) {
 
 // split_of for every launched GEMM (split_for: the GEMM and its kernel
 // alone decide); a split GEMM runs its kernel uncapped (its runs are meant
-// to spread over the GPU; a cap changes where a tile runs, never its sum).
+// to spread over the GPU; a cap changes where a tile runs, never its sum),
+// and so does one that runs of kMinSplitKTiles would split: its capped variant
+// was tuned split, over the whole GPU ((512, 2048, 2048) bf16 tn on 64 x 64
+// tiles capped at 64 CUs 21.1 us, uncapped 12.7, in two runs 17.5).
 // A split GEMM whose planes no longer fit in what its group has left of the
 // kSplitWsBytes workspace keeps its split and moves to a group appended
 // after the others (filled greedily in launch order), so the workspace
@@ -892,7 +903,8 @@ void plan_splits(const gdy_ctx* ctx, const gdy_gemm* g, gdy_plan_t* p, int mode)
     const int i = p->order[t];
     if (p->variant_of[i] < 0) continue;
     const int s = split_for(ctx, p->variant_of[i], g[i]);
-    if (s > 1) p->variant_of[i] = ctx->variants[p->variant_of[i]].uncapped;
+    if (split_count(ctx, p->variant_of[i], g[i], kMinSplitKTiles, kMinSplitKTiles) > 1)
+      p->variant_of[i] = ctx->variants[p->variant_of[i]].uncapped;
     p->split_of[i] = s;
   }
   if (mode == GDY_SEQUENTIAL) return;

@@ -100,6 +100,14 @@ def test_split_count_hand_values(ctx, shape, kernel, batch, want):
     assert p["split_of"][0] == want
 
 
+def test_fp32_splits_at_16_k_tiles(ctx):
+    # (256, 1024, 1024) on 16x64: 16 x 16 = 256 tiles, one a CU, and 1024/32 = 32 K tiles: 2 x 16
+    for k, want in ((1024, 2), (992, 1)):
+        d = desc(256, 1024, k, 0, v(ctx, "f32_nn_16x64_w1x4_m16_c0"))
+        d.a_type = d.b_type = d.c_type = 4
+        assert ctx.plan([d], mode="forced")["split_of"][0] == want
+
+
 @pytest.mark.parametrize("shape,kernel,batch,want", [c for c in SPLIT_CASES if c[3] > 1])
 def test_split_does_not_depend_on_co_runners(ctx, shape, kernel, batch, want):
     """The same GEMM on the same kernel splits the same way alone, in a group
@@ -121,6 +129,9 @@ def test_capped_variant_splits_uncapped(ctx):
     assert p["split_of"][0] == 8 and p["variant_of"][0] == v(ctx, K64 + "_c0")
     p = ctx.plan([desc(16, 1024, 1024, 0, v(ctx, K64 + "_c64"))], mode="forced")
     assert p["split_of"][0] == 1 and p["variant_of"][0] == v(ctx, K64 + "_c64")
+    # 256 tiles of 32 K tiles: two runs of 16 would fit, but every CU has a tile: unsplit, and uncapped all the same
+    p = ctx.plan([desc(512, 2048, 2048, 0, v(ctx, K64 + "_c64"))], mode="forced")
+    assert p["split_of"][0] == 1 and p["variant_of"][0] == v(ctx, K64 + "_c0")
 
 
 # --------------------------------------------------------------------------
